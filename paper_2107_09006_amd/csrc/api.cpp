@@ -1846,8 +1846,20 @@ lsq2l_status lsq2l_transpose(int32_t m, int32_t n, int32_t nnz, const int32_t* r
   // the sort carries the permutation; a caller that does not want it gets
   // a temporary one.  The last 256 bytes hold the column check flag.
   const size_t perm_bytes = tperm ? 0 : ((size_t)nnz * sizeof(int32_t) + 255) / 256 * 256;
-  void* temp = nullptr;
-  LSQ2L_HIP_TRY(hipMalloc(&temp, tb + perm_bytes + 256));
+  // work space from the cache of destroyed handles' blocks, where it goes
+  // back after the last synchronization
+  const size_t want = tb + perm_bytes + 256;
+  size_t held = 0;
+  int dev = 0;
+  LSQ2L_HIP_TRY(hipGetDevice(&dev));
+  void* temp = cache_take(want, dev, &held);
+  if (!temp) {
+    if (hipMalloc(&temp, want) != hipSuccess) {
+      cache_release();
+      LSQ2L_HIP_TRY(hipMalloc(&temp, want));
+    }
+    held = want;
+  }
   int32_t* perm = tperm ? tperm : (int32_t*)((char*)temp + tb);
   int32_t* flag = (int32_t*)((char*)temp + tb + perm_bytes);
   int32_t hflag = 0;
@@ -1857,7 +1869,8 @@ lsq2l_status lsq2l_transpose(int32_t m, int32_t n, int32_t nnz, const int32_t* r
   if (e == hipSuccess && hflag == 0)
     e = launch_transpose(st, m, n, nnz, rowptr, colind, vals, trowptr, trow, tvals, perm, temp, tb);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(temp);
+  if (e == hipSuccess) cache_give(temp, held, dev);
+  else (void)hipFree(temp);
   if (e != hipSuccess) {
     set_error(std::string("transpose: ") + hipGetErrorString(e));
     return LSQ2L_EHIP;

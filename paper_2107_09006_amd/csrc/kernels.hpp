@@ -73,7 +73,8 @@ void launch_permute_rows(hipStream_t st, int32_t m, const int32_t* perm, const i
                          const int32_t* colind, const double* vals, const int32_t* prowptr,
                          int32_t* pcolind, double* pvals);
 // trowptr (n + 1), trow and tperm (nnz) written; tvals written if not null
-// (vals must then be given); temp holds transpose_temp_bytes(nnz, n) bytes
+// (vals must then be given); temp holds transpose_temp_bytes(nnz, n) bytes, or
+// fewer if they are enough for the narrow digits
 hipError_t launch_transpose(hipStream_t st, int32_t m, int32_t n, int64_t nnz, const int32_t* rowptr,
                             const int32_t* colind, const double* vals, int32_t* trowptr,
                             int32_t* trow, double* tvals, int32_t* tperm, void* temp,
