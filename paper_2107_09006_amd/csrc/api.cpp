@@ -332,19 +332,51 @@ void apply_M(lsq2l_ctx* c, const double* r, double* z) {
   scatter(c, c->loc, c->coarse ? c->dvec : nullptr, z, false);
 }
 
-// per-instance sums of the RED_BLOCKS partials (host, fixed order)
-lsq2l_status read_seg_sums(lsq2l_ctx* c, const double* partial, std::vector<double>& out) {
-  const int S = c->S;
-  LSQ2L_HIP_TRY(hipMemcpyAsync(c->h_part, partial, sizeof(double) * S * RED_BLOCKS,
-                               hipMemcpyDeviceToHost, c->st));
+Reduction reduction(lsq2l_ctx* c, int op, double tol) {
+  Reduction R{};
+  R.op = op;
+  R.two = 0;
+  R.tol = tol;
+  R.partial = c->partial;
+  R.count = c->red_count;
+  R.out = c->sums;
+  R.lsqr = c->lsqr.sc;
+  R.sc = c->sc;
+  return R;
+}
+
+void dot(lsq2l_ctx* c, const Segments& G, const double* a, const double* b, const Reduction& R) {
+  RedVec V;
+  V.a = a;
+  V.b = b;
+  launch_reduce(c->st, RED_DOT, G, V, R);
+}
+
+namespace {
+
+// the sums of an OP_SUM reduction
+lsq2l_status read_sums(lsq2l_ctx* c, std::vector<double>& out) {
+  LSQ2L_HIP_TRY(hipMemcpyAsync(c->h_part, c->sums, sizeof(double) * c->S, hipMemcpyDeviceToHost, c->st));
   LSQ2L_HIP_TRY(hipStreamSynchronize(c->st));
-  out.assign(S, 0.0);
-  for (int s = 0; s < S; ++s) {
-    double t = 0.0;
-    for (int b = 0; b < RED_BLOCKS; ++b) t += c->h_part[(size_t)s * RED_BLOCKS + b];
-    out[s] = t;
-  }
+  out.assign(c->h_part, c->h_part + c->S);
   return LSQ2L_OK;
+}
+
+}  // namespace
+
+lsq2l_status host_dot(lsq2l_ctx* c, const double* a, const double* b, std::vector<double>& out) {
+  dot(c, c->cols(), a, b, reduction(c, OP_SUM));
+  return read_sums(c, out);
+}
+
+lsq2l_status host_sub_norm2(lsq2l_ctx* c, const double* a, const double* b, double* out,
+                            std::vector<double>& nrm2) {
+  RedVec V;
+  V.a = a;
+  V.b = b;
+  V.o = out;
+  launch_reduce(c->st, RED_SUB, c->cols(), V, reduction(c, OP_SUM));
+  return read_sums(c, nrm2);
 }
 
 // ||C||_2 per instance, from below, by 30 steps of the power method on C
@@ -356,15 +388,13 @@ lsq2l_status norm_C(lsq2l_ctx* c) {
   const int64_t n = c->M.n;
   double* v = c->rold;
   double* w = c->q;
-  double* nrm = c->sc.pq;          // S doubles, free outside the iteration
+  double* nrm = c->sums;
   launch_hash_fill(st, n, v);
-  launch_dot(st, S, c->d_seg_col, v, v, c->partial);
-  launch_seg_sum(st, S, c->partial, nrm);
+  dot(c, c->cols(), v, v, reduction(c, OP_SUM));
   launch_normalize_seg(st, n, S, c->d_seg_col, nrm, nullptr, v, v);
   for (int it = 0; it < 30; ++it) {
     apply_C(c, v, w, c->tm);
-    launch_dot(st, S, c->d_seg_col, w, w, c->partial);
-    launch_seg_sum(st, S, c->partial, nrm);
+    dot(c, c->cols(), w, w, reduction(c, OP_SUM));
     launch_normalize_seg(st, n, S, c->d_seg_col, nrm, nullptr, w, v);
   }
   std::vector<double> h(S);
@@ -385,10 +415,32 @@ lsq2l_status read_flags(lsq2l_ctx* c) {
   return LSQ2L_OK;
 }
 
-// The residual-norm step of a CG iteration (sets the done flags).
-void rnorm_step(lsq2l_ctx* c, double tol2, int flexible) {
-  launch_dot(c->st, c->S, c->d_seg_col, c->r, c->r, c->partial);
-  launch_scalar(c->st, OP_RNORM, c->S, c->partial, nullptr, c->sc, tol2, flexible);
+// The steps of a CG iteration around M r.  x += alpha p, r -= alpha q with
+// alpha = rho / p^T q and the residual norm, which sets the done flags (also
+// on the host); with flexible, the old r is kept.
+void cg_step(lsq2l_ctx* c, double* x, double tol2) {
+  apply_C(c, c->p, c->q, c->tm);
+  dot(c, c->cols(), c->p, c->q, reduction(c, OP_ALPHA));
+  RedVec V;
+  V.a = c->p;
+  V.b = c->q;
+  V.o = x;
+  V.o2 = c->r;
+  V.keep = c->opt.flexible ? c->rold : nullptr;
+  launch_reduce(c->st, RED_AXPY, c->cols(), V, reduction(c, OP_RNORM, tol2));
+}
+
+// p = z + beta p after z = M r
+void cg_direction(lsq2l_ctx* c) {
+  apply_M(c, c->r, c->z);
+  RedVec V;
+  V.a = c->r;
+  V.b = c->z;
+  V.c = c->rold;
+  Reduction R = reduction(c, OP_BETA);
+  R.two = c->opt.flexible ? 1 : 0;
+  launch_reduce(c->st, R.two ? RED_DOT2 : RED_DOT, c->cols(), V, R);
+  launch_xpby(c->st, c->cols(), c->sc.beta, c->z, c->p);
 }
 
 // One PCG iteration as a HIP graph: both SpMVs, alpha, the x and r update,
@@ -400,25 +452,12 @@ lsq2l_status capture_iteration(lsq2l_ctx* c, double* x, double tol2, hipGraphExe
   *out = nullptr;
   if (!c->gst) LSQ2L_HIP_TRY(hipStreamCreateWithFlags(&c->gst, hipStreamNonBlocking));
   const hipStream_t saved = c->st;
-  const int S = c->S;
-  const int64_t n = c->M.n;
-  const int flexible = c->opt.flexible;
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamBeginCapture(c->gst, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     c->st = c->gst;
-    const hipStream_t st = c->st;
-    apply_C(c, c->p, c->q, c->tm);
-    launch_dot(st, S, c->d_seg_col, c->p, c->q, c->partial);
-    launch_scalar(st, OP_ALPHA, S, c->partial, nullptr, c->sc, tol2, flexible);
-    if (flexible) launch_copy(st, n, c->r, c->rold);
-    launch_axpy_xr(st, n, S, c->d_seg_col, c->sc.alpha, c->p, c->q, x, c->r);
-    rnorm_step(c, tol2, flexible);
-    apply_M(c, c->r, c->z);
-    launch_dot(st, S, c->d_seg_col, c->r, c->z, c->partial);
-    if (flexible) launch_dot(st, S, c->d_seg_col, c->rold, c->z, c->partial2);
-    launch_scalar(st, OP_BETA, S, c->partial, flexible ? c->partial2 : nullptr, c->sc, tol2, flexible);
-    launch_xpby(st, n, S, c->d_seg_col, c->sc.beta, c->z, c->p);
+    cg_step(c, x, tol2);
+    cg_direction(c);
     c->st = saved;
     e = hipStreamEndCapture(c->gst, &g);
   }
@@ -444,12 +483,13 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
   const int S = c->S;
   const int64_t n = c->M.n;
   const double tol2 = tol * tol;
-  const int flexible = c->opt.flexible;
-  launch_fill(st, n, 0.0, x);
-  launch_fill_i32(st, S, 0, c->sc.its);
-  launch_copy(st, n, c->rhs, c->r);
-  launch_dot(st, S, c->d_seg_col, c->r, c->r, c->partial);
-  launch_scalar(st, OP_R0, S, c->partial, nullptr, c->sc, tol2, flexible);
+  {
+    RedVec V;
+    V.a = c->rhs;
+    V.o = x;
+    V.o2 = c->r;
+    launch_reduce(st, RED_START, c->cols(), V, reduction(c, OP_R0));
+  }
   int its = 0, restarts = 0;
   bool breakdown = false;
   res.relres.assign(S, 0.0);
@@ -458,9 +498,13 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
   res.converged.assign(S, 0);
   while (true) {
     apply_M(c, c->r, c->z);
-    launch_dot(st, S, c->d_seg_col, c->r, c->z, c->partial);
-    launch_scalar(st, OP_RHO_INIT, S, c->partial, nullptr, c->sc, tol2, flexible);
-    launch_copy(st, n, c->z, c->p);
+    {
+      RedVec V;
+      V.a = c->r;
+      V.b = c->z;
+      V.o = c->p;
+      launch_reduce(st, RED_COPY, c->cols(), V, reduction(c, OP_RHO_INIT));
+    }
     TRY(read_flags(c));
     bool all_done = true;
     for (int s = 0; s < S; ++s) all_done &= (c->h_done[s] != 0);
@@ -477,8 +521,12 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
       }
       ++its;
       if (its % std::max(1, c->opt.check_every) == 0 || its >= c->opt.max_it) {
-        const lsq2l_status fs = read_flags(c);
-        if (fs != LSQ2L_OK) { (void)hipGraphExecDestroy(gexec); return fs; }
+        const hipError_t se = hipStreamSynchronize(st);    // h_done is written by the iteration
+        if (se != hipSuccess) {
+          (void)hipGraphExecDestroy(gexec);
+          set_error(std::string("PCG iteration graph: ") + hipGetErrorString(se));
+          return LSQ2L_EHIP;
+        }
         all_done = true;
         for (int s = 0; s < S; ++s) {
           all_done &= (c->h_done[s] != 0);
@@ -488,15 +536,10 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
     }
     if (gexec) (void)hipGraphExecDestroy(gexec);
     while (!all_done && its < c->opt.max_it) {
-      apply_C(c, c->p, c->q, c->tm);
-      launch_dot(st, S, c->d_seg_col, c->p, c->q, c->partial);
-      launch_scalar(st, OP_ALPHA, S, c->partial, nullptr, c->sc, tol2, flexible);
-      if (flexible) launch_copy(st, n, c->r, c->rold);
-      launch_axpy_xr(st, n, S, c->d_seg_col, c->sc.alpha, c->p, c->q, x, c->r);
-      rnorm_step(c, tol2, flexible);
+      cg_step(c, x, tol2);
       ++its;
       if (its % std::max(1, c->opt.check_every) == 0 || its >= c->opt.max_it) {
-        TRY(read_flags(c));
+        LSQ2L_HIP_TRY(hipStreamSynchronize(st));           // h_done is written by the iteration
         all_done = true;
         for (int s = 0; s < S; ++s) {
           all_done &= (c->h_done[s] != 0);
@@ -504,22 +547,13 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
         }
         if (all_done) break;
       }
-      apply_M(c, c->r, c->z);
-      launch_dot(st, S, c->d_seg_col, c->r, c->z, c->partial);
-      if (flexible) launch_dot(st, S, c->d_seg_col, c->rold, c->z, c->partial2);
-      launch_scalar(st, OP_BETA, S, c->partial, flexible ? c->partial2 : nullptr, c->sc, tol2, flexible);
-      launch_xpby(st, n, S, c->d_seg_col, c->sc.beta, c->z, c->p);
+      cg_direction(c);
     }
     // true residual rhs - A^T A x
     apply_C(c, x, c->q, c->tm);
-    launch_sub(st, n, c->rhs, c->q, c->q);
-    launch_dot(st, S, c->d_seg_col, c->q, c->q, c->partial);
     std::vector<double> t2, x2;
-    TRY(read_seg_sums(c, c->partial, t2));
-    if (adjoint) {
-      launch_dot(st, S, c->d_seg_col, x, x, c->partial2);
-      TRY(read_seg_sums(c, c->partial2, x2));
-    }
+    TRY(host_sub_norm2(c, c->rhs, c->q, c->q, t2));
+    if (adjoint) TRY(host_dot(c, x, x, x2));
     TRY(read_flags(c));
     bool all_ok = true;
     const bool last = restarts == 3 || its >= c->opt.max_it;
@@ -542,7 +576,7 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
     ++restarts;
     launch_copy(st, n, c->q, c->r);
     launch_fill_i32(st, S, 0, c->sc.done);
-    rnorm_step(c, tol2, flexible);
+    dot(c, c->cols(), c->r, c->r, reduction(c, OP_RNORM, tol2));
   }
   LSQ2L_HIP_TRY(hipMemcpyAsync(c->h_its, c->sc.its, sizeof(int32_t) * S, hipMemcpyDeviceToHost, st));
   LSQ2L_HIP_TRY(hipStreamSynchronize(st));
@@ -562,19 +596,12 @@ lsq2l_status pcg(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResult
 // instance (and ||x||^2 if asked), through the work vectors q and tm.
 lsq2l_status true_residual(lsq2l_ctx* c, const double* x, std::vector<double>& rel,
                            std::vector<double>* x2) {
-  const hipStream_t st = c->st;
   const int S = c->S;
   apply_C(c, x, c->q, c->tm);
-  launch_sub(st, c->M.n, c->rhs, c->q, c->q);
   std::vector<double> t2, r2;
-  launch_dot(st, S, c->d_seg_col, c->q, c->q, c->partial);
-  TRY(read_seg_sums(c, c->partial, t2));
-  launch_dot(st, S, c->d_seg_col, c->rhs, c->rhs, c->partial);
-  TRY(read_seg_sums(c, c->partial, r2));
-  if (x2) {
-    launch_dot(st, S, c->d_seg_col, x, x, c->partial);
-    TRY(read_seg_sums(c, c->partial, *x2));
-  }
+  TRY(host_sub_norm2(c, c->rhs, c->q, c->q, t2));
+  TRY(host_dot(c, c->rhs, c->rhs, r2));
+  if (x2) TRY(host_dot(c, x, x, *x2));
   rel.assign(S, 0.0);
   for (int s = 0; s < S; ++s) rel[s] = r2[s] > 0 ? std::sqrt(t2[s] / r2[s]) : 0.0;
   return LSQ2L_OK;
@@ -1259,8 +1286,13 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
   }
   TRY(c->dalloc(&c->bsave, m));
   TRY(c->dalloc(&c->loc, H.total_loc));
-  TRY(c->dalloc(&c->partial, (int64_t)S * RED_BLOCKS));
-  TRY(c->dalloc(&c->partial2, (int64_t)S * RED_BLOCKS));
+  TRY(c->dalloc(&c->partial, 2 * (int64_t)S * RED_BLOCKS));
+  TRY(c->dalloc(&c->sums, S));
+  {
+    const int64_t len = (int64_t)std::min(S, RED_TOTAL / 2) * COUNT_LEN;
+    TRY(c->dalloc(&c->red_count, len));
+    launch_fill_i32(st, len, 0, c->red_count);
+  }
   double* scal = nullptr;
   TRY(c->dalloc(&scal, 6 * (int64_t)S));
   c->sc.rho = scal; c->sc.alpha = scal + S; c->sc.beta = scal + 2 * S;
@@ -1271,7 +1303,12 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
   TRY(c->halloc(&c->h_its, S));
   TRY(c->halloc(&c->h_rn2, S));
   TRY(c->halloc(&c->h_r0n2, S));
-  TRY(c->halloc(&c->h_part, (int64_t)S * RED_BLOCKS));
+  TRY(c->halloc(&c->h_part, S));
+  c->sc.h_done = c->h_done;
+  for (int s = 0; s < S; ++s) {
+    c->max_seg_col = std::max(c->max_seg_col, c->seg_col_h[s + 1] - c->seg_col_h[s]);
+    c->max_seg_row = std::max(c->max_seg_row, c->seg_row_h[s + 1] - c->seg_row_h[s]);
+  }
   TRY(c->upload(&c->d_seg_col, c->seg_col_h));
   TRY(c->upload(&c->d_seg_row, c->seg_row_h));
   TRY(krylov_alloc(c));

@@ -68,9 +68,10 @@ struct GmresWork {
   double* V = nullptr;                       // column j at V + j n
   double *w = nullptr, *z = nullptr, *t = nullptr;   // n
   double* part = nullptr;                    // multi-dot partials
+  int32_t* count = nullptr;                  // multi-dot counters, zero between launches
   double* h = nullptr;                       // (restart + 1) per instance, reduced
   double* y = nullptr;                       // (restart + 1) per instance
-  double* nrm = nullptr;                     // per instance
+  double* nrm = nullptr;                     // per instance, right after h
   double* h_h = nullptr;                     // pinned copies
   double* h_y = nullptr;
 };
@@ -92,6 +93,9 @@ struct lsq2l_ctx {
   std::vector<int64_t> seg_row_h, seg_col_h;
   int64_t* d_seg_row = nullptr;
   int64_t* d_seg_col = nullptr;
+  int64_t max_seg_row = 0, max_seg_col = 0;   // the longest instance
+  lsq2l::Segments rows() const { return {d_seg_row, S, max_seg_row}; }
+  lsq2l::Segments cols() const { return {d_seg_col, S, max_seg_col}; }
   lsq2l::DevMatrix M;
   lsq2l::DevMatrix Mi;      // row-permuted copy of A and its transpose for C p = A^T (A p)
   bool row_perm = false;    // Mi is in use
@@ -123,7 +127,8 @@ struct lsq2l_ctx {
   double *X = nullptr, *W = nullptr, *efac = nullptr, *edinv = nullptr, *einv = nullptr;
   double *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *rhs = nullptr, *rold = nullptr;
   double *tm = nullptr, *tm2 = nullptr, *loc = nullptr, *cvec = nullptr, *dvec = nullptr;
-  double *partial = nullptr, *partial2 = nullptr, *xwork = nullptr;
+  double *partial = nullptr, *sums = nullptr, *xwork = nullptr;
+  int32_t* red_count = nullptr;  // counters of the reductions, zero between launches
   double *bsave = nullptr, *xsave = nullptr;
   double *bal_u = nullptr, *bal_w = nullptr;   // balanced / deflated forms: two n-vectors
   bool have_solution = false;
@@ -133,7 +138,7 @@ struct lsq2l_ctx {
   int32_t* h_its = nullptr;       // pinned
   double* h_rn2 = nullptr;        // pinned
   double* h_r0n2 = nullptr;       // pinned
-  double* h_part = nullptr;       // pinned, S * RED_BLOCKS
+  double* h_part = nullptr;       // pinned, S
   std::vector<double> normC;      // ||C||_2 per instance (power iteration), empty until needed
   lsq2l::LsqrWork lsqr;
   lsq2l::GmresWork gmres;

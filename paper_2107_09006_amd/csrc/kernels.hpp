@@ -114,43 +114,62 @@ void launch_grad_vals(hipStream_t st, int32_t m, const int32_t* rowptr, const in
                       double* out);
 
 // --- vector / reduction kernels --------------------------------------------
-constexpr int RED_BLOCKS = 256;   // partial sums per segment
-void launch_dot(hipStream_t st, int S, const int64_t* seg_ptr, const double* a, const double* b,
-                double* partial);
-enum ScalarOp { OP_R0 = 0, OP_RHO_INIT = 1, OP_ALPHA = 2, OP_RNORM = 3, OP_BETA = 4 };
+constexpr int RED_BLOCKS = 256;   // most partial sums per segment
+constexpr int RED_TOTAL = 8192;   // most workgroups of a reduction with more than one per segment
+// counters of the workgroups of a segment: one per COUNT_GROUP of them and
+// one for the groups, COUNT_STRIDE int32 apart (128 bytes)
+constexpr int COUNT_GROUP = 16, COUNT_STRIDE = 32;
+constexpr int COUNT_LEN = (1 + RED_BLOCKS / COUNT_GROUP) * COUNT_STRIDE;
+// the instances' parts of a concatenated vector (device offsets), and the longest
+struct Segments {
+  const int64_t* ptr;
+  int S;
+  int64_t maxlen;
+};
+enum ScalarOp { OP_R0 = 0, OP_RHO_INIT = 1, OP_ALPHA = 2, OP_RNORM = 3, OP_BETA = 4, OP_SUM = 5,
+                LSQR_INIT_BETA = 8, LSQR_INIT_ALPHA = 9, LSQR_BETA = 10, LSQR_ALPHA = 11 };
 struct Scalars {
   double *rho, *alpha, *beta, *rn2, *r0n2, *pq;
   int32_t* done;      // 0 active, 1 converged, 2 breakdown
   int32_t* its;       // iterations of each instance (x updated while active)
+  int32_t* h_done;    // pinned host copy of done, written by every OP_RNORM
 };
-void launch_scalar(hipStream_t st, int op, int S, const double* partial, const double* partial2,
-                   Scalars sc, double tol2, int flexible);
-void launch_axpy_xr(hipStream_t st, int64_t n, int S, const int64_t* seg_ptr, const double* alpha,
-                    const double* p, const double* q, double* x, double* r);
-void launch_xpby(hipStream_t st, int64_t n, int S, const int64_t* seg_ptr, const double* beta,
-                 const double* z, double* p);
+// LSQR: per-instance scalars, LSQR_NSC per instance
+enum LsqrSc { LS_ALPHA = 0, LS_BETA, LS_RHOBAR, LS_PHIBAR, LS_ANORM2, LS_T1, LS_T2, LS_TEST,
+              LS_RNORM0, LS_NSC };
+constexpr int LSQR_NSC = LS_NSC;
+// What a reduction does with its sums (per segment): op, and its operands.
+// partial holds 2 RED_BLOCKS doubles per segment; count COUNT_LEN int32 per
+// segment, zero between launches (with more than RED_TOTAL / 2 segments every
+// segment is one workgroup, and none of the two is touched).
+struct Reduction {
+  int op;
+  int two;            // the pass forms two sums
+  double tol;         // OP_RNORM: squared tolerance; LSQR_ALPHA: tolerance
+  double* partial;
+  int32_t* count;
+  double* out;        // OP_SUM
+  double* lsqr;       // LSQR scalars
+  Scalars sc;
+};
+// the vectors of a pass (see k_reduce)
+enum { RED_DOT = 0, RED_DOT2, RED_COPY, RED_START, RED_SUB, RED_AXPY, RED_LSQR };
+struct RedVec {
+  const double *a = nullptr, *b = nullptr, *c = nullptr;
+  double *o = nullptr, *o2 = nullptr, *keep = nullptr;
+  int first = 0;
+};
+void launch_reduce(hipStream_t st, int kind, const Segments& G, const RedVec& V, const Reduction& R);
+void launch_xpby(hipStream_t st, const Segments& G, const double* beta, const double* z, double* p);
 void launch_sub(hipStream_t st, int64_t n, const double* a, const double* b, double* out);
 void launch_add(hipStream_t st, int64_t n, const double* a, const double* b, double* out);
 void launch_fill(hipStream_t st, int64_t n, double v, double* out);
 void launch_copy(hipStream_t st, int64_t n, const double* a, double* out);
-// out_k = a_k * f[segment of k] (per-instance factors on the device)
-void launch_scale_seg(hipStream_t st, int64_t n, int S, const int64_t* seg_ptr, const double* f,
-                      const double* a, double* out);
 void launch_fill_i32(hipStream_t st, int64_t n, int32_t v, int32_t* out);
 // a fixed pseudo-random vector in [-1, 1) (start of the power method)
 void launch_hash_fill(hipStream_t st, int64_t n, double* out);
 
 // --- LSQR (left-preconditioned, M^{-1} inner product) ------------------------
-// per-instance scalars, LSQR_NSC per instance at sc + s * LSQR_NSC
-enum LsqrSc { LS_ALPHA = 0, LS_BETA, LS_RHOBAR, LS_PHIBAR, LS_ANORM2, LS_T1, LS_T2, LS_TEST,
-              LS_RNORM0, LS_NSC };
-constexpr int LSQR_NSC = LS_NSC;
-enum LsqrOp { LSQR_INIT_BETA = 0, LSQR_INIT_ALPHA = 1, LSQR_BETA = 2, LSQR_ALPHA = 3 };
-void launch_lsqr_scalar(hipStream_t st, int op, int S, const double* partial, double* sc,
-                        int32_t* done, int32_t* its, double tol);
-// u = a - alpha u (m-space, row segments; active instances only)
-void launch_lsqr_u(hipStream_t st, int64_t m, int S, const int64_t* seg_row, const double* sc,
-                   const int32_t* done, const double* a, double* u, int first);
 // u *= 1 / beta (m-space)
 void launch_lsqr_unorm(hipStream_t st, int64_t m, int S, const int64_t* seg_row, const double* sc,
                        const int32_t* done, double* u);
@@ -163,12 +182,13 @@ void launch_lsqr_update(hipStream_t st, int64_t n, int S, const int64_t* seg_col
                         double* v, double* w, double* x, int first);
 
 // --- GMRES -------------------------------------------------------------------
-// partial[(s * RED_BLOCKS + b) * ld + i] = chunk b of segment s of V_i . w, i < k
-void launch_multidot(hipStream_t st, int S, const int64_t* seg_ptr, int64_t n, int k,
-                     const double* V, const double* w, double* partial, int ld);
-// h[s * ld + i] (+)= sum_b partial (fixed order), i < k
-void launch_multidot_reduce(hipStream_t st, int S, int k, const double* partial, int ld,
-                            double* h, int accumulate);
+// h[s * ld + i] = V_i . w over segment s (i < k); sum (may be null) += h
+// partial: RED_BLOCKS * ld doubles per segment; count: COUNT_STRIDE int32 per
+// segment and MDOT vectors, zero between launches
+constexpr int MDOT = 8;           // vectors of one workgroup
+void launch_multidot(hipStream_t st, const Segments& G, int64_t n, int k, const double* V,
+                     const double* w, double* partial, int32_t* count, int ld, double* h,
+                     double* sum);
 // w -= sum_{i<k} V_i h[s * ld + i]
 void launch_multi_axpy(hipStream_t st, int S, const int64_t* seg_ptr, int64_t n, int k,
                        const double* V, const double* h, int ld, double* w);
@@ -178,8 +198,6 @@ void launch_multi_gemv(hipStream_t st, int S, const int64_t* seg_ptr, int64_t n,
 // out_k = a_k / sqrt(nrm2[segment]) (0 where the norm is zero or the instance is done)
 void launch_normalize_seg(hipStream_t st, int64_t n, int S, const int64_t* seg_ptr,
                           const double* nrm2, const int32_t* done, const double* a, double* out);
-// norm2[s] = sum_b partial[s * RED_BLOCKS + b]
-void launch_seg_sum(hipStream_t st, int S, const double* partial, double* out);
 
 // --- subdomain kernels -------------------------------------------------------
 void launch_gather_values(hipStream_t st, int64_t nnz, const int32_t* perm, const double* src,

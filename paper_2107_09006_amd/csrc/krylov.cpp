@@ -39,9 +39,12 @@ lsq2l_status krylov_alloc(lsq2l_ctx* c) {
     TRY(c->dalloc(&G.z, n));
     TRY(c->dalloc(&G.t, n));
     TRY(c->dalloc(&G.part, (int64_t)S * RED_BLOCKS * ld));
-    TRY(c->dalloc(&G.h, (int64_t)S * ld));
+    const int64_t counters = (int64_t)S * ((ld + MDOT - 1) / MDOT) * COUNT_STRIDE;
+    TRY(c->dalloc(&G.count, counters));
+    launch_fill_i32(c->st, counters, 0, G.count);
+    TRY(c->dalloc(&G.h, (int64_t)S * ld + S));
+    G.nrm = G.h + (int64_t)S * ld;
     TRY(c->dalloc(&G.y, (int64_t)S * ld));
-    TRY(c->dalloc(&G.nrm, S));
     TRY(c->halloc(&G.h_h, (int64_t)S * ld + S));
     TRY(c->halloc(&G.h_y, (int64_t)S * ld));
   }
@@ -60,16 +63,21 @@ lsq2l_status lsqr(lsq2l_ctx* c, const double* b, double* x, double tol, KrylovRe
   int32_t* its = c->sc.its;
   launch_fill(st, n, 0.0, x);
   // beta_1 u_1 = b
-  launch_copy(st, m, b, L.u);
-  launch_dot(st, S, c->d_seg_row, L.u, L.u, c->partial);
-  launch_lsqr_scalar(st, LSQR_INIT_BETA, S, c->partial, L.sc, done, its, tol);
+  launch_fill_i32(st, S, 0, done);
+  auto u_step = [&](const double* a, int first, int op) {
+    RedVec V;
+    V.a = a;
+    V.o = L.u;
+    V.first = first;
+    launch_reduce(st, RED_LSQR, c->rows(), V, reduction(c, op));
+  };
+  u_step(b, 1, LSQR_INIT_BETA);
   launch_lsqr_unorm(st, m, S, c->d_seg_row, L.sc, done, L.u);
   // alpha_1: q = A^T u_1, s = M q, alpha_1 = sqrt(q^T s)
   spmv_AT(c, L.u, L.q);
   launch_lsqr_q(st, n, S, c->d_seg_col, L.sc, done, L.zh, L.q, 1);
   apply_M(c, L.q, L.s);
-  launch_dot(st, S, c->d_seg_col, L.q, L.s, c->partial);
-  launch_lsqr_scalar(st, LSQR_INIT_ALPHA, S, c->partial, L.sc, done, its, tol);
+  dot(c, c->cols(), L.q, L.s, reduction(c, LSQR_INIT_ALPHA));
   launch_lsqr_update(st, n, S, c->d_seg_col, L.sc, done, L.q, L.s, L.zh, L.v, L.w, x, 1);
   std::vector<int32_t> hd(S);
   auto flags = [&](bool& all_stop, bool& brk) -> lsq2l_status {
@@ -89,16 +97,13 @@ lsq2l_status lsqr(lsq2l_ctx* c, const double* b, double* x, double tol, KrylovRe
   while (!all_stop && it < c->opt.max_it) {
     // beta u = A vt - alpha u
     spmv_A(c, L.v, L.Av);
-    launch_lsqr_u(st, m, S, c->d_seg_row, L.sc, done, L.Av, L.u, 0);
-    launch_dot(st, S, c->d_seg_row, L.u, L.u, c->partial);
-    launch_lsqr_scalar(st, LSQR_BETA, S, c->partial, L.sc, done, its, tol);
+    u_step(L.Av, 0, LSQR_BETA);
     launch_lsqr_unorm(st, m, S, c->d_seg_row, L.sc, done, L.u);
     // alpha: q = A^T u - beta zh, s = M q
     spmv_AT(c, L.u, L.q);
     launch_lsqr_q(st, n, S, c->d_seg_col, L.sc, done, L.zh, L.q, 0);
     apply_M(c, L.q, L.s);
-    launch_dot(st, S, c->d_seg_col, L.q, L.s, c->partial);
-    launch_lsqr_scalar(st, LSQR_ALPHA, S, c->partial, L.sc, done, its, tol);
+    dot(c, c->cols(), L.q, L.s, reduction(c, LSQR_ALPHA, tol));
     launch_lsqr_update(st, n, S, c->d_seg_col, L.sc, done, L.q, L.s, L.zh, L.v, L.w, x, 0);
     ++it;
     if (it % std::max(1, c->opt.check_every) == 0 || it >= c->opt.max_it) TRY(flags(all_stop, brk));
@@ -138,8 +143,7 @@ lsq2l_status gmres(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResu
   const int R = G.restart, ld = R + 1;
   launch_fill(st, n, 0.0, x);
   std::vector<double> rhs2, x2(S, 0.0), beta(S);
-  launch_dot(st, S, c->d_seg_col, c->rhs, c->rhs, c->partial);
-  TRY(read_seg_sums(c, c->partial, rhs2));
+  TRY(host_dot(c, c->rhs, c->rhs, rhs2));
   std::vector<int32_t> state(S, 0);        // 0 active, 1 converged, 2 breakdown
   std::vector<int32_t> its(S, 0);
   std::vector<double> est(S, 0.0);
@@ -160,14 +164,9 @@ lsq2l_status gmres(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResu
   while (true) {
     // true residual w = rhs - C x of every instance
     apply_C(c, x, c->q, c->tm);
-    launch_sub(st, n, c->rhs, c->q, G.w);
     std::vector<double> r2;
-    launch_dot(st, S, c->d_seg_col, G.w, G.w, c->partial);
-    TRY(read_seg_sums(c, c->partial, r2));
-    if (adjoint) {
-      launch_dot(st, S, c->d_seg_col, x, x, c->partial);
-      TRY(read_seg_sums(c, c->partial, x2));
-    }
+    TRY(host_sub_norm2(c, c->rhs, c->q, G.w, r2));
+    if (adjoint) TRY(host_dot(c, x, x, x2));
     bool all_stop = true;
     for (int s = 0; s < S; ++s) {
       beta[s] = std::sqrt(r2[s]);
@@ -182,8 +181,9 @@ lsq2l_status gmres(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResu
     // V_0 = w / beta on the active instances (zero elsewhere)
     for (int s = 0; s < S; ++s) hdone[s] = state[s] != 0;
     LSQ2L_HIP_TRY(hipMemcpyAsync(c->sc.done, hdone.data(), sizeof(int32_t) * S, hipMemcpyHostToDevice, st));
-    launch_dot(st, S, c->d_seg_col, G.w, G.w, c->partial);
-    launch_seg_sum(st, S, c->partial, G.nrm);
+    Reduction norm = reduction(c, OP_SUM);
+    norm.out = G.nrm;
+    dot(c, c->cols(), G.w, G.w, norm);
     launch_normalize_seg(st, n, S, c->d_seg_col, G.nrm, c->sc.done, G.w, G.V);
     for (int s = 0; s < S; ++s) {
       std::fill(g[s].begin(), g[s].end(), 0.0);
@@ -197,18 +197,13 @@ lsq2l_status gmres(lsq2l_ctx* c, double* x, bool adjoint, double tol, KrylovResu
       apply_M(c, Vj, G.z);
       apply_C(c, G.z, G.w, c->tm);
       // two passes of classical Gram-Schmidt against V_0 .. V_j
-      launch_multidot(st, S, c->d_seg_col, n, j + 1, G.V, G.w, G.part, ld);
-      launch_multidot_reduce(st, S, j + 1, G.part, ld, G.h, 0);
+      launch_multidot(st, c->cols(), n, j + 1, G.V, G.w, G.part, G.count, ld, G.h, nullptr);
       launch_multi_axpy(st, S, c->d_seg_col, n, j + 1, G.V, G.h, ld, G.w);
-      launch_multidot(st, S, c->d_seg_col, n, j + 1, G.V, G.w, G.part, ld);
-      launch_multidot_reduce(st, S, j + 1, G.part, ld, G.y, 0);
+      launch_multidot(st, c->cols(), n, j + 1, G.V, G.w, G.part, G.count, ld, G.y, G.h);
       launch_multi_axpy(st, S, c->d_seg_col, n, j + 1, G.V, G.y, ld, G.w);
-      launch_multidot_reduce(st, S, j + 1, G.part, ld, G.h, 1);
-      launch_dot(st, S, c->d_seg_col, G.w, G.w, c->partial);
-      launch_seg_sum(st, S, c->partial, G.nrm);
+      dot(c, c->cols(), G.w, G.w, norm);
       launch_normalize_seg(st, n, S, c->d_seg_col, G.nrm, c->sc.done, G.w, G.V + (int64_t)(j + 1) * n);
-      LSQ2L_HIP_TRY(hipMemcpyAsync(G.h_h, G.h, sizeof(double) * S * ld, hipMemcpyDeviceToHost, st));
-      LSQ2L_HIP_TRY(hipMemcpyAsync(G.h_h + (size_t)S * ld, G.nrm, sizeof(double) * S, hipMemcpyDeviceToHost, st));
+      LSQ2L_HIP_TRY(hipMemcpyAsync(G.h_h, G.h, sizeof(double) * S * (ld + 1), hipMemcpyDeviceToHost, st));
       LSQ2L_HIP_TRY(hipStreamSynchronize(st));
       ++total;
       bool cycle_done = true;

@@ -26,7 +26,14 @@ void spmv_AT(lsq2l_ctx* c, const double* y, double* x);
 void apply_C(lsq2l_ctx* c, const double* x, double* y, double* tmp);
 void apply_M(lsq2l_ctx* c, const double* r, double* z);
 void local_solves(lsq2l_ctx* c);
-lsq2l_status read_seg_sums(lsq2l_ctx* c, const double* partial, std::vector<double>& out);
+// a reduction over the columns or rows of every instance that takes step op
+Reduction reduction(lsq2l_ctx* c, int op, double tol = 0.0);
+void dot(lsq2l_ctx* c, const Segments& G, const double* a, const double* b, const Reduction& R);
+// per-instance sums a . b on the host (synchronizes)
+lsq2l_status host_dot(lsq2l_ctx* c, const double* a, const double* b, std::vector<double>& out);
+// out = a - b over the columns, and its squared norms on the host
+lsq2l_status host_sub_norm2(lsq2l_ctx* c, const double* a, const double* b, double* out,
+                            std::vector<double>& nrm2);
 lsq2l_status true_residual(lsq2l_ctx* c, const double* x, std::vector<double>& rel,
                            std::vector<double>* x2);
 lsq2l_status norm_C(lsq2l_ctx* c);
