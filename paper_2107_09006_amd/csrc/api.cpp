@@ -175,6 +175,13 @@ lsq2l_status lsq2l_ctx::raw_alloc(void** v, size_t bytes) {
   int dev = 0;
   LSQ2L_HIP_TRY(hipGetDevice(&dev));
   size_t got = 0;
+  // eight sizes per power of two: problems that are alike ask for the same
+  // blocks, and a setup on new inputs finds what an earlier one left (with
+  // the sizes as asked, irregular matrices of 1e6 columns took 182 ms instead
+  // of 96 on new inputs)
+  size_t step = (size_t)1 << 20;
+  while (step * 16 <= bytes) step *= 2;
+  bytes = (bytes + step - 1) / step * step;
   if ((*v = cache_take(bytes, dev, &got)) != nullptr) {
     dev_allocs.push_back({*v, got, dev});
     return LSQ2L_OK;
@@ -234,20 +241,20 @@ void apply_C(lsq2l_ctx* c, const double* x, double* y, double* tmp) {
   spmv_it_AT(c, tmp, y);
 }
 
-void local_solves(lsq2l_ctx* c) {
+void local_solves(lsq2l_ctx* c, const double* r) {
   if (c->opt.precision == LSQ2L_MIXED)
-    launch_local_solve_f32(c->st, c->nsub, c->Ps, c->fac32, c->dinv32, c->loc);
+    launch_local_solve<float>(c->st, c->nsub, c->Ps, c->ss, c->fac32, c->dinv32, r, c->loc);
   else if (c->solve_plan)
-    launch_local_solve(c->st, c->nsub, c->Ps, c->sfac, c->sdinv, c->loc);
+    launch_local_solve<double>(c->st, c->nsub, c->Ps, c->ss, c->sfac, c->sdinv, r, c->loc);
   else
-    launch_local_solve(c->st, c->nsub, c->P, c->fac, c->dinv, c->loc);
+    launch_local_solve<double>(c->st, c->nsub, c->P, c->ss, c->fac, c->dinv, r, c->loc);
 }
 
 namespace {
 
 void scatter(lsq2l_ctx* c, const double* loc, const double* dcoarse, double* z, bool restricted) {
-  if (c->X32) launch_scatter_local(c->st, c->M.n, c->P, c->scale, loc, c->X32, dcoarse, z, restricted);
-  else launch_scatter_local(c->st, c->M.n, c->P, c->scale, loc, c->X, dcoarse, z, restricted);
+  if (c->X32) launch_scatter_local(c->st, c->M.n, c->P, loc, c->X32, dcoarse, z, restricted);
+  else launch_scatter_local(c->st, c->M.n, c->P, loc, c->X, dcoarse, z, restricted);
 }
 
 // z = Q r = R_0^T E^{-1} R_0 r (restriction, symmetric E^{-1} product, prolongation)
@@ -262,8 +269,7 @@ void apply_Q(lsq2l_ctx* c, const double* r, double* z) {
 // z = M_ASM r = sum_i R_i^T C_ii^{-1} R_i r (eq. one_level_schwarz), or with
 // `restricted` M_RAS r = sum_i R_i^T D_i C_ii^{-1} R_i r (eq. RAS)
 void apply_one_level(lsq2l_ctx* c, const double* r, double* z, bool restricted) {
-  launch_gather_local(c->st, c->nsub, c->P, c->scale, r, c->loc);
-  local_solves(c);
+  local_solves(c, r);
   scatter(c, c->loc, nullptr, z, restricted);
 }
 
@@ -322,8 +328,7 @@ void apply_M(lsq2l_ctx* c, const double* r, double* z) {
   // (eq. two_level_schwarz), the coarse restriction and solve between the
   // local solves and the scatter that adds both
   const hipStream_t st = c->st;
-  launch_gather_local(st, c->nsub, c->P, c->scale, r, c->loc);
-  local_solves(c);
+  local_solves(c, r);
   if (c->coarse) {
     if (c->X32) launch_coarse_restrict(st, c->nsub, c->P, c->max_p, c->X32, r, c->cvec);
     else launch_coarse_restrict(st, c->nsub, c->P, c->max_p, c->X, r, c->cvec);
@@ -669,9 +674,9 @@ lsq2l_status solve_layout_begin(lsq2l_ctx* c) {
   c->sl_loc = lo;
   TRY(c->upload(&c->sl_dg, c->sl_g));
   TRY(c->dalloc(&c->sl_inv, H.total_loc));
-  TRY(c->dalloc(&c->sl_Fg, std::max<int64_t>(tb, 1)));
+  TRY(c->dalloc(&c->sl_F8, std::max<int64_t>(4 * tb, 1)));
   launch_solve_inv(st, c->nsub, c->P, c->sl_inv);
-  launch_solve_env_init(st, c->nsub, c->sl_dg, c->sl_Fg);
+  launch_solve_env_init(st, c->nsub, c->sl_dg, c->sl_F8);
   return LSQ2L_OK;
 }
 
@@ -692,22 +697,23 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   c->info.solve_permuted = 0;
   if (!c->sl_inv) return LSQ2L_OK;
   const std::vector<SubDesc>& g = c->sl_g;
-  const int64_t tb = c->sl_tiles, lo = c->sl_loc;
+  const int64_t lo = c->sl_loc;
   int32_t* inv = c->sl_inv;
-  std::vector<int32_t> hF((size_t)tb);
-  if (tb) LSQ2L_HIP_TRY(hipMemcpyAsync(hF.data(), c->sl_Fg, sizeof(int32_t) * tb, hipMemcpyDeviceToHost, st));
+  int32_t* d_tiles = nullptr;
+  std::vector<int32_t> hT(nsub);
+  TRY(c->dalloc(&d_tiles, nsub));
+  launch_layout_count(st, nsub, c->sl_dg, c->sl_F8, d_tiles);
+  LSQ2L_HIP_TRY(hipMemcpyAsync(hT.data(), d_tiles, sizeof(int32_t) * nsub, hipMemcpyDeviceToHost, st));
   LSQ2L_HIP_TRY(hipStreamSynchronize(st));
   // choose per subdomain, then the layout's offsets
   std::vector<SubDesc> s(g);
-  std::vector<int32_t> sF;
-  std::vector<int64_t> sOff, tiles(nsub);
-  int64_t ftiles = 0, dtiles = 0, stb = 0, split_tiles = 0;
+  std::vector<int64_t> tiles(nsub);
+  int64_t ftiles = 0, dtiles = 0, split_tiles = 0;
   int permuted = 0;
   for (int i = 0; i < nsub; ++i) {
     const SubDesc& m = H.subs[i];
-    int64_t tm = 0, tg = 0;
-    for (int32_t t = 0; t < m.ntiles; ++t) tm += t - H.tileF[m.tile_base + t] + 1;
-    for (int32_t t = 0; t < g[i].ntiles; ++t) tg += t - hF[g[i].tile_base + t] + 1;
+    const int64_t end = i + 1 < nsub ? H.subs[i + 1].fac_off : H.total_fac;
+    const int64_t tm = (end - m.fac_off) / TT, tg = hT[i];
     split_tiles += tm;
     const int order = c->opt.solve_order;
     const bool use_g = order == LSQ2L_ORDER_GLOBAL || (order == LSQ2L_ORDER_AUTO && tg * 100 <= tm * 85);
@@ -715,18 +721,12 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
     d.np = use_g ? g[i].np : m.np;
     d.ntiles = use_g ? g[i].ntiles : m.ntiles;
     d.spare = use_g ? 1 : 0;
-    d.tile_base = stb; stb += d.ntiles;
+    d.tile_base = dtiles;
     d.fac_off = ftiles * TT;
-    d.dinv_off = dtiles * TT; dtiles += d.ntiles;
-    int64_t run = 0;
-    for (int32_t t = 0; t < d.ntiles; ++t) {
-      const int32_t f = use_g ? hF[g[i].tile_base + t] : H.tileF[m.tile_base + t];
-      sF.push_back(f);
-      sOff.push_back(run);
-      run += t - f + 1;
-    }
-    ftiles += run;
-    tiles[i] = run;
+    d.dinv_off = dtiles * TT;
+    dtiles += d.ntiles;
+    tiles[i] = use_g ? tg : tm;
+    ftiles += tiles[i];
     permuted += use_g;
   }
   c->info.split_tiles = split_tiles;
@@ -735,7 +735,7 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   c->solve_plan = true;
   c->s_total_fac = ftiles * TT;
   c->s_total_dinv = dtiles * TT;
-  c->s_total_tiles = stb;
+  c->s_total_tiles = dtiles;
   c->s_total_np = 0;
   DevPlan& Ps = c->Ps;
   Ps.max_np = 0;
@@ -747,17 +747,57 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   for (int i = 0; i < nsub; ++i) so[i] = s[order[i]];
   TRY(c->upload(&Ps.subs, s));
   TRY(c->upload(&Ps.subs_ord, so));
-  TRY(c->upload(&Ps.solve_order, order));
-  TRY(c->upload(&Ps.tileF, sF));
-  TRY(c->upload(&Ps.tileOff, sOff));
+  TRY(c->dalloc(&Ps.tileF, dtiles));
+  TRY(c->dalloc(&Ps.tileOff, dtiles));
+  launch_layout_fill(st, nsub, c->P, Ps.subs, c->sl_dg, c->sl_F8, Ps.tileF, Ps.tileOff);
   TRY(c->dalloc(&Ps.sperm, std::max<int64_t>(lo, 1)));
   launch_fill_i32(st, lo, -1, Ps.sperm);
   launch_solve_perm(st, nsub, c->P, Ps.subs, inv, Ps.sperm);
-  if (Ps.max_np > 12544) TRY(c->dalloc(&Ps.yscratch, std::max<int64_t>(lo, 1)));
+  if (Ps.max_np > local_solve_cap()) TRY(c->dalloc(&Ps.yscratch, std::max<int64_t>(lo, 1)));
   TRY(c->dalloc(s64, std::max<int64_t>(c->s_total_fac, 1)));
   if (qr) LSQ2L_HIP_TRY(hipMemsetAsync(*s64, 0, c->s_total_fac * sizeof(double), st));
   else launch_gather_solve(st, nsub, c->P, Ps, c->fac, *s64);
   return LSQ2L_OK;
+}
+
+// The streams of the local solves in the layout P: space, tables and gather
+// maps, enqueued on st (the entries follow the factors, pack_solve_stream).
+lsq2l_status solve_stream(lsq2l_ctx* c, hipStream_t st) {
+  const bool own = c->solve_plan;
+  const DevPlan& Lay = own ? c->Ps : c->P;
+  SolveStream& S = c->ss;
+  const int64_t tiles = (own ? c->s_total_fac : c->H.total_fac) / TT;
+  const int64_t rows = (own ? c->s_total_dinv : c->H.total_dinv) / TT;
+  const int64_t locs = own ? c->sl_loc : c->H.total_loc;
+  const size_t eb = c->opt.precision == LSQ2L_MIXED ? sizeof(float) : sizeof(double);
+  char *f = nullptr, *b = nullptr, *dp = nullptr;
+  TRY(c->dalloc(&f, (int64_t)((tiles + 1) * TT * eb)));
+  TRY(c->dalloc(&b, (int64_t)((tiles + 1) * TT * eb)));
+  TRY(c->dalloc(&dp, (int64_t)(rows * SOLVE_DPACK * eb)));
+  S.fwd = f;
+  S.bwd = b;
+  S.dpack = dp;
+  for (int dir = 0; dir < 2; ++dir) {
+    TRY(c->dalloc(&S.nfar[dir], rows));
+    TRY(c->dalloc(&S.pos[dir], 4 * tiles));
+    TRY(c->dalloc(&S.desc[dir], 4 * (tiles + 1)));
+  }
+  TRY(c->dalloc(&S.far0, SOLVE_FAR_INTS * (int64_t)c->nsub));
+  TRY(c->dalloc(&S.scol, locs));
+  TRY(c->dalloc(&S.sscale, locs));
+  launch_stream_layout(st, c->nsub, Lay, c->sl_F8, c->sl_dg, tiles, S);
+  launch_solve_cols(st, c->nsub, c->P, Lay, c->scale, S);
+  return LSQ2L_OK;
+}
+
+// The streams' entries from the finished solve factors.
+void pack_solve_stream(lsq2l_ctx* c, hipStream_t st) {
+  if (c->opt.precision == LSQ2L_MIXED)
+    launch_stream_pack<float>(st, c->nsub, c->Ps, c->fac32, c->dinv32, c->ss);
+  else if (c->solve_plan)
+    launch_stream_pack<double>(st, c->nsub, c->Ps, c->sfac, c->sdinv, c->ss);
+  else
+    launch_stream_pack<double>(st, c->nsub, c->P, c->fac, c->dinv, c->ss);
 }
 
 // Everything after the matrix is resident in the handle (c->M rowptr/colind/vals).
@@ -835,7 +875,6 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
       tiles[i] = f1 - f0;
     }
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tiles[x] > tiles[y]; });
-    TRY(c->upload(&c->P.solve_order, order));
     TRY(upload_ordered());
     static std::once_flag once;
     static hipError_t conf = hipSuccess;
@@ -860,17 +899,17 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
     // QR local factors (Remarks 3.1, 3.2): no C_ii is formed.  The pattern
     // pass of the assembly still gives the envelope of the global-order
     // layouts; the equilibration's scaling comes from the column norms of A.
-    if (c->sl_inv) launch_assemble(st, nparts, c->P, c->M, nullptr, nullptr, c->sl_inv, c->sl_dg, c->sl_Fg);
+    if (c->sl_inv) launch_assemble(st, nparts, c->P, c->M, nullptr, nullptr, c->sl_inv, c->sl_dg, c->sl_F8);
     launch_col_scale(st, nparts, c->P, c->M, c->scale);
   } else if (c->opt.diag_shift_rel <= 0.0) {
     // S = diag(C_ii)^{-1/2} = 1 / ||A(:, c)|| first, then S C_ii S and
     // S Ct_GG S assembled in one pass
     c->shift = 0.0;
     launch_col_scale(st, nparts, c->P, c->M, c->scale);
-    launch_assemble(st, nparts, c->P, c->M, c->fac, c->ctg, c->sl_inv, c->sl_dg, c->sl_Fg,
+    launch_assemble(st, nparts, c->P, c->M, c->fac, c->ctg, c->sl_inv, c->sl_dg, c->sl_F8,
                     c->scale);
   } else {
-  launch_assemble(st, nparts, c->P, c->M, c->fac, c->ctg, c->sl_inv, c->sl_dg, c->sl_Fg);
+  launch_assemble(st, nparts, c->P, c->M, c->fac, c->ctg, c->sl_inv, c->sl_dg, c->sl_F8);
   // Global shift of Section 4.1 ("Setup phase"): the preconditioner is built
   // for C + s I, s = diag_shift_rel ||C||_F, i.e. for the least-squares
   // matrix [A; sqrt(s) I].  Its rows sqrt(s) e_j enter Xi_i for j in
@@ -928,6 +967,10 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
     LSQ2L_HIP_TRY(hipMemsetAsync(qstrip, 0, strip_len * sizeof(double), st));
   } else {
     launch_chol_local(st, nparts, c->P, c->fac, c->dinv, c->status, c->solve_plan);
+    if (!c->solve_plan) {
+      TRY(solve_stream(c, st));
+      pack_solve_stream(c, st);
+    }
   }
   if (c->solve_plan) {
     double* qdinv = nullptr;     // FP64 inverse diagonal tiles of the QR solve factors
@@ -965,6 +1008,8 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
     } else {
       launch_chol_local(c->st2, nparts, c->Ps, c->sfac, c->sdinv, c->status + 2);
     }
+    TRY(solve_stream(c, c->st2));
+    pack_solve_stream(c, c->st2);
     LSQ2L_HIP_TRY(hipEventRecord(c->ev_join, c->st2));
   }
   if (qr)
@@ -1004,6 +1049,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
       launch_chol_local(st, nparts, c->Ps, s64, d64, c->status + 3);
       launch_to_float(st, c->s_total_fac, s64, c->fac32);
       launch_to_float(st, c->s_total_dinv, d64, c->dinv32);
+      pack_solve_stream(c, st);
       LSQ2L_HIP_TRY(hipMemcpyAsync(&hs, c->status + 3, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       LSQ2L_HIP_TRY(hipStreamSynchronize(st));
       if (hs != 0) {
@@ -1791,13 +1837,21 @@ lsq2l_status lsq2l_time_kernel(lsq2l_handle c, int32_t kernel, int32_t reps, dou
   switch (kernel) {
     case 0: *bytes = 12.0 * nnz + 4.0 * (m + 1) + 8.0 * n + 8.0 * m; break;
     case 1: *bytes = 12.0 * nnz + 4.0 * (n + 1) + 8.0 * m + 8.0 * n; break;
-    // each sweep reads every stored off-diagonal tile and every diagonal
-    // inverse once (as many elements as the stored factor), plus y in and out
-    case 2:
-      *bytes = c->solve_plan
-                   ? 2.0 * eb * (double)c->s_total_fac + (16.0 + 8.0) * (double)c->s_total_np
-                   : 2.0 * eb * (double)c->H.total_fac + 16.0 * (double)c->H.total_loc;
+    // the packed diagonal inverses twice, the chain tiles and slabs of both
+    // sweeps, their tables, and the gather and result per local unknown
+    case 2: {
+      std::vector<int32_t> far((size_t)c->nsub * SOLVE_FAR_INTS);
+      LSQ2L_HIP_TRY(hipMemcpyAsync(far.data(), c->ss.far0, far.size() * sizeof(int32_t),
+                                   hipMemcpyDeviceToHost, c->st));
+      LSQ2L_HIP_TRY(hipStreamSynchronize(c->st));
+      const double rows = (double)(c->solve_plan ? c->s_total_dinv : c->H.total_dinv) / TT;
+      double slabs = 0;
+      for (int i = 0; i < c->nsub; ++i)
+        for (int dir = 1; dir <= 2; ++dir) slabs += far[(size_t)i * SOLVE_FAR_INTS + dir * (SOLVE_FAR_INTS / 2) - 1];
+      *bytes = eb * (rows * 2.0 * (SOLVE_DPACK + TT) + slabs * TS * 8) + 4.0 * slabs +
+               (4.0 + 8.0 + 8.0 + 8.0 + 4.0 + 8.0) * rows * TS;
       break;
+    }
     // the algorithmic minimum: each sweep reads the nnz(L_i) entries of the
     // factors under a fill-reducing order, y in and out per local unknown
     case 4: {
@@ -1820,7 +1874,6 @@ lsq2l_status lsq2l_time_kernel(lsq2l_handle c, int32_t kernel, int32_t reps, dou
   }
   launch_fill(c->st, c->M.n, 1.0, c->p);
   launch_fill(c->st, c->M.m, 1.0, c->tm);
-  launch_fill(c->st, c->H.total_loc, 1.0, c->loc);
   if (c->coarse) launch_fill(c->st, c->n0tot, 1.0, c->cvec);
   hipEvent_t e0, e1;
   LSQ2L_HIP_TRY(hipEventCreate(&e0));
@@ -1830,7 +1883,7 @@ lsq2l_status lsq2l_time_kernel(lsq2l_handle c, int32_t kernel, int32_t reps, dou
       case 0: spmv_it_A(c, c->p, c->tm); break;
       case 1: spmv_it_AT(c, c->tm, c->q); break;
       case 2:
-      case 4: local_solves(c); break;
+      case 4: local_solves(c, c->p); break;
       default: launch_einv_gemv(c->st, c->n0tot, c->S, c->Cc, c->einv, c->cvec, c->dvec);
     }
   };

@@ -22,7 +22,7 @@ __global__ void k_gather_values(int64_t nnz, const int32_t* __restrict__ perm,
 }
 
 // Lower triangle of C_ii (tile-envelope layout) and of Ct_GG (dense, ld nGp);
-// with fac null, only the envelope Fg below.
+// with fac null, only the envelope F8 below.
 // Thread per local column: every write of a thread lands in its own column,
 // so the accumulation order is fixed and no atomics are needed.  Workgroup
 // (i, y) takes the columns y * 256 + t, (y + gridDim.y) * 256 + t, ... of
@@ -30,7 +30,8 @@ __global__ void k_gather_values(int64_t nnz, const int32_t* __restrict__ perm,
 // With inv given, it also finds the tile envelope of C_ii in the global
 // column order (see k_solve_inv): the thread of column a sees every column
 // coupled to it, so the first coupled position of row inv[a] in that order
-// is the minimum it meets, one atomicMin per column into Fg.
+// is the minimum it meets, one atomicMin per column into F8 (one entry per
+// eight rows).
 // With scl given (S = diag(C_ii)^{-1/2} per local position, which is
 // 1 / ||A(:, c)||: C_ii holds whole columns of A), every product is scaled as
 // it is added, so the result is S C_ii S and S Ct_GG S directly, with unit
@@ -43,7 +44,7 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
            const int32_t* __restrict__ trow, const double* __restrict__ tvals,
            const int32_t* __restrict__ tileF, const int64_t* __restrict__ tileOff,
            double* __restrict__ fac, double* __restrict__ ctg, const int32_t* __restrict__ inv,
-           const SubDesc* __restrict__ gsub, int32_t* __restrict__ Fg,
+           const SubDesc* __restrict__ gsub, int32_t* __restrict__ F8,
            const double* __restrict__ scl) {
   const SubDesc d = subs[blockIdx.x];
   const int i = d.id;
@@ -78,7 +79,7 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
         if (inxi && a >= d.nI) Ct[(int64_t)(posa - d.nIp) * d.nGp + (posc - d.nIp)] += v;
       }
     }
-    if (iv) atomicMin(&Fg[gsub[i].tile_base + qa / TS], fmin / TS);
+    if (iv) atomicMin(&F8[4 * gsub[i].tile_base + qa / 8], fmin);
   }
   if (A && sl && blockIdx.y == 0)
     for (int pos = threadIdx.x; pos < d.np; pos += blockDim.x) {
@@ -311,11 +312,73 @@ k_solve_inv(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
   }
 }
 
-// Fg[tile_base + t] = t for every tile row t of the global-order layout
+// F8[4 tile_base + g] = 8 g for every group g of eight rows of the global-order layout
 __global__ void __launch_bounds__(256)
-k_solve_env_init(const SubDesc* __restrict__ gsub, int32_t* __restrict__ Fg) {
+k_solve_env_init(const SubDesc* __restrict__ gsub, int32_t* __restrict__ F8) {
   const SubDesc g = gsub[blockIdx.x];
-  for (int t = threadIdx.x; t < g.ntiles; t += blockDim.x) Fg[g.tile_base + t] = t;
+  for (int t = threadIdx.x; t < 4 * g.ntiles; t += blockDim.x) F8[4 * g.tile_base + t] = 8 * t;
+}
+
+// first tile column of tile row t from the envelope of its four row groups
+__device__ inline int first_tile(const int32_t* f8, int t) {
+  return min(min(f8[4 * t], f8[4 * t + 1]), min(f8[4 * t + 2], f8[4 * t + 3])) / TS;
+}
+
+// sum of v over the workgroup's threads before this one; the total in *total
+__device__ inline int block_excl_sum_256(int v, int* sh, int* total) {
+  const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  __syncthreads();
+  if (lane == 63) sh[w] = x;
+  __syncthreads();
+  int before = 0;
+  for (int q = 0; q < w; ++q) before += sh[q];
+  *total = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  return before + x - v;
+}
+
+// tiles[i] = tiles of the envelope of subdomain i's global-order layout
+__global__ void __launch_bounds__(256)
+k_layout_count(const SubDesc* __restrict__ gsub, const int32_t* __restrict__ F8, int32_t* __restrict__ tiles) {
+  __shared__ int sh[4];
+  const SubDesc g = gsub[blockIdx.x];
+  const int32_t* f8 = F8 + 4 * g.tile_base;
+  int v = 0, total = 0;
+  for (int t = threadIdx.x; t < g.ntiles; t += 256) v += t - first_tile(f8, t) + 1;
+  (void)block_excl_sum_256(v, sh, &total);
+  if (threadIdx.x == 0) tiles[blockIdx.x] = total;
+}
+
+// envelope tables of the chosen layouts: from F8 where ssub.spare is set, else
+// those of the [I, Gamma] layout; offsets are the running tile counts
+__global__ void __launch_bounds__(256)
+k_layout_fill(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF,
+              const SubDesc* __restrict__ ssub, const SubDesc* __restrict__ gsub,
+              const int32_t* __restrict__ F8, int32_t* __restrict__ stileF, int64_t* __restrict__ stileOff) {
+  __shared__ int sh[4];
+  const SubDesc d = subs[blockIdx.x];
+  const SubDesc s = ssub[d.id];
+  const int32_t* f8 = F8 + 4 * gsub[d.id].tile_base;
+  int run = 0;
+  for (int t0 = 0; t0 < s.ntiles; t0 += 256) {
+    const int t = t0 + threadIdx.x;
+    int f = 0, n = 0, total = 0;
+    if (t < s.ntiles) {
+      f = s.spare ? first_tile(f8, t) : tileF[d.tile_base + t];
+      n = t - f + 1;
+    }
+    const int before = run + block_excl_sum_256(n, sh, &total);
+    if (t < s.ntiles) {
+      stileF[s.tile_base + t] = f;
+      stileOff[s.tile_base + t] = before;
+    }
+    run += total;
+  }
 }
 
 // sperm[loc_off + q] = loc index of the entry the solve layout holds at
@@ -393,31 +456,13 @@ __global__ void k_to_float(int64_t n, const double* __restrict__ src, float* __r
   if (k < n) dst[k] = (float)src[k];
 }
 
-// loc_i = S_i R_i r (padding zero)
-__global__ void __launch_bounds__(256)
-k_gather_local(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
-               const double* __restrict__ scale, const double* __restrict__ r,
-               double* __restrict__ loc) {
-  const SubDesc d = subs[blockIdx.x];
-  const int32_t* om = omega + d.omega_off;
-  for (int pos = threadIdx.x; pos < d.np; pos += blockDim.x) {
-    double v = 0.0;
-    if (pos < d.nI) v = r[om[pos]];
-    else if (pos >= d.nIp && pos < d.nIp + d.nG) v = r[om[d.nI + pos - d.nIp]];
-    loc[d.loc_off + pos] = scale[d.loc_off + pos] * v;
-  }
-}
-
-
-// z_j = sum over the subdomains holding column j of S_pos loc_pos (fixed
-// order), plus the coarse prolongation X_i d_i on the interior of its owner.
+// z_j = sum over the subdomains holding column j of loc_pos (fixed order), plus the coarse prolongation X_i d_i on the interior of its owner.
 // Without loc only the prolongation is formed, without dcoarse only the sum.
 // With `restricted`, column j takes only the value of its own subdomain's
 // interior (R_i^T D_i of eq. RAS: D_i is zero on Omega_Gamma_i).
 template <typename TX>
 __global__ void k_scatter_local(int32_t n, const int32_t* __restrict__ own_ptr,
-                                const int32_t* __restrict__ own_pos, const double* __restrict__ scale,
-                                const double* __restrict__ loc, const int32_t* __restrict__ part,
+                                const int32_t* __restrict__ own_pos, const double* __restrict__ loc, const int32_t* __restrict__ part,
                                 const int32_t* __restrict__ locown, const SubDesc* __restrict__ subs,
                                 const TX* __restrict__ X, const double* __restrict__ dcoarse,
                                 double* __restrict__ z, int restricted) {
@@ -427,11 +472,10 @@ __global__ void k_scatter_local(int32_t n, const int32_t* __restrict__ own_ptr,
   if (loc != nullptr) {
     if (restricted) {
       const int64_t pos = subs[part[j]].loc_off + locown[j];
-      s = scale[pos] * loc[pos];
+      s = loc[pos];
     } else {
       for (int q = own_ptr[j]; q < own_ptr[j + 1]; ++q) {
-        const int pos = own_pos[q];
-        s += scale[pos] * loc[pos];
+        s += loc[own_pos[q]];
       }
     }
   }
@@ -462,14 +506,14 @@ void launch_gather_values(hipStream_t st, int64_t nnz, const int32_t* perm, cons
 }
 
 void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, double* fac,
-                     double* ctg, const int32_t* inv, const SubDesc* gsub, int32_t* Fg,
+                     double* ctg, const int32_t* inv, const SubDesc* gsub, int32_t* F8,
                      const double* scale) {
   // workgroups per subdomain: enough for the largest one to take 2 columns
   // per thread (at most 64)
   const int ny = std::max(1, std::min(64, (P.max_np + 511) / 512));
   k_assemble<<<dim3(nsub, ny), 256, 0, st>>>(P.heavy(), P.omega, P.part, P.locown, M.rowptr,
                                              M.colind, M.vals, M.trowptr, M.trow, M.tvals, P.tileF,
-                                             P.tileOff, fac, ctg, inv, gsub, Fg, scale);
+                                             P.tileOff, fac, ctg, inv, gsub, F8, scale);
 }
 
 void launch_equilibrate(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* ctg,
@@ -488,8 +532,17 @@ void launch_solve_inv(hipStream_t st, int nsub, const DevPlan& P, int32_t* inv) 
   k_solve_inv<<<nsub, 256, 0, st>>>(P.heavy(), P.omega, inv);
 }
 
-void launch_solve_env_init(hipStream_t st, int nsub, const SubDesc* gsub, int32_t* Fg) {
-  k_solve_env_init<<<nsub, 256, 0, st>>>(gsub, Fg);
+void launch_layout_count(hipStream_t st, int nsub, const SubDesc* gsub, const int32_t* F8, int32_t* tiles) {
+  k_layout_count<<<nsub, 256, 0, st>>>(gsub, F8, tiles);
+}
+
+void launch_layout_fill(hipStream_t st, int nsub, const DevPlan& P, const SubDesc* ssub,
+                        const SubDesc* gsub, const int32_t* F8, int32_t* tileF, int64_t* tileOff) {
+  k_layout_fill<<<nsub, 256, 0, st>>>(P.heavy(), P.tileF, ssub, gsub, F8, tileF, tileOff);
+}
+
+void launch_solve_env_init(hipStream_t st, int nsub, const SubDesc* gsub, int32_t* F8) {
+  k_solve_env_init<<<nsub, 256, 0, st>>>(gsub, F8);
 }
 
 void launch_solve_perm(hipStream_t st, int nsub, const DevPlan& P, const SubDesc* ssub,
@@ -513,27 +566,18 @@ void launch_to_float(hipStream_t st, int64_t n, const double* src, float* dst) {
   k_to_float<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, src, dst);
 }
 
-void launch_gather_local(hipStream_t st, int nsub, const DevPlan& P, const double* scale,
-                         const double* r, double* loc) {
-  k_gather_local<<<nsub, 256, 0, st>>>(P.subs, P.omega, scale, r, loc);
-}
-
-
-
-void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* scale,
-                          const double* loc, const double* X, const double* dcoarse, double* z,
-                          bool restricted) {
+void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* loc,
+                          const double* X, const double* dcoarse, double* z, bool restricted) {
   if (n == 0) return;
-  k_scatter_local<double><<<(n + 255) / 256, 256, 0, st>>>(n, P.own_ptr, P.own_pos, scale, loc,
+  k_scatter_local<double><<<(n + 255) / 256, 256, 0, st>>>(n, P.own_ptr, P.own_pos, loc,
                                                            P.part, P.locown, P.subs, X, dcoarse, z,
                                                            restricted ? 1 : 0);
 }
 
-void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* scale,
-                          const double* loc, const float* X, const double* dcoarse, double* z,
-                          bool restricted) {
+void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* loc,
+                          const float* X, const double* dcoarse, double* z, bool restricted) {
   if (n == 0) return;
-  k_scatter_local<float><<<(n + 255) / 256, 256, 0, st>>>(n, P.own_ptr, P.own_pos, scale, loc,
+  k_scatter_local<float><<<(n + 255) / 256, 256, 0, st>>>(n, P.own_ptr, P.own_pos, loc,
                                                           P.part, P.locown, P.subs, X, dcoarse, z,
                                                           restricted ? 1 : 0);
 }

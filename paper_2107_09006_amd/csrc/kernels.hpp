@@ -31,9 +31,8 @@ struct DevPlan {              // subdomain layout (device copies of HostPlan)
   int64_t* tileOff = nullptr;
   int32_t* own_ptr = nullptr;
   int32_t* own_pos = nullptr;
-  int32_t* solve_order = nullptr;  // subdomains by decreasing stored factor tiles
-  SubDesc* subs_ord = nullptr;     // subs in that order: the one-workgroup-per-subdomain
-                                   // setup kernels start the largest subdomains first
+  SubDesc* subs_ord = nullptr;     // subs by decreasing stored factor tiles: launches with
+                                   // one workgroup per subdomain start the largest first
   int max_np = 0;             // largest padded local size
   int min_nG = 0, max_nG = 0;  // least and largest interface size
   // layout of the solve factor only: where each position lives in the local
@@ -42,6 +41,21 @@ struct DevPlan {              // subdomain layout (device copies of HostPlan)
   int32_t* sperm = nullptr;
   double* yscratch = nullptr;
   const SubDesc* heavy() const { return subs_ord ? subs_ord : subs; }
+};
+
+constexpr int SOLVE_DPACK = 640;      // entries of a packed diagonal inverse
+constexpr int SOLVE_FAR_INTS = 14;    // entries of SolveStream::far0 per subdomain
+// What the local solves read (k_solve.hip): the streams of both sweeps and
+// the packed diagonal inverses, in the type of the factors, with their tables
+struct SolveStream {
+  void *fwd = nullptr, *bwd = nullptr;    // as many entries as the factor's envelope, and a tile
+  void* dpack = nullptr;                  // SOLVE_DPACK entries per diagonal tile
+  uint16_t* nfar[2] = {nullptr, nullptr}; // slabs of every step (tile_base + step)
+  int32_t* pos[2] = {nullptr, nullptr};   // per tile and group of eight: its slab, -1: none
+  int32_t* desc[2] = {nullptr, nullptr};  // per slab: its group of eight
+  int32_t* far0 = nullptr;                // per subdomain and sweep: first slab of each helper, count
+  int32_t* scol = nullptr;                // per position: global column (-1: padding)
+  double* sscale = nullptr;               // and its scaling
 };
 
 struct DevCoarse {            // coarse space and coarse operator
@@ -202,13 +216,13 @@ void launch_normalize_seg(hipStream_t st, int64_t n, int S, const int64_t* seg_p
 // --- subdomain kernels -------------------------------------------------------
 void launch_gather_values(hipStream_t st, int64_t nnz, const int32_t* perm, const double* src,
                           double* dst);
-// with inv (not null), also the tile envelope Fg of the global-order
-// layouts gsub (Fg set by launch_solve_env_init first)
+// with inv (not null), also the envelope F8 of the global-order layouts gsub:
+// per eight rows the first position they reach (launch_solve_env_init first)
 // scale non-null: assemble S C_ii S and S Ct_GG S directly (S = scale, from
 // launch_col_scale), identity on the padding diagonal
 void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, double* fac,
                      double* ctg, const int32_t* inv = nullptr, const SubDesc* gsub = nullptr,
-                     int32_t* Fg = nullptr, const double* scale = nullptr);
+                     int32_t* F8 = nullptr, const double* scale = nullptr);
 void launch_equilibrate(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* ctg,
                         double* scale);
 // interior_only: factor the interior tile columns only (L_I and L_GI)
@@ -219,10 +233,11 @@ void launch_chol_local_f32(hipStream_t st, int nsub, const DevPlan& P, float* fa
                            int32_t* status);
 // solve factor in the global-column order of each subdomain: inv (indexed
 // like loc) maps an [I, Gamma] position to its global-order position;
-// gsub describes the global-order layout (np, ntiles, tile_base); Fg,
-// initialized here to the diagonal, gets its tile envelope from the assembly
+// gsub describes the global-order layout (np, ntiles, tile_base); F8 (four per
+// tile row), initialized here to the diagonal, gets its envelope from the
+// assembly
 void launch_solve_inv(hipStream_t st, int nsub, const DevPlan& P, int32_t* inv);
-void launch_solve_env_init(hipStream_t st, int nsub, const SubDesc* gsub, int32_t* Fg);
+void launch_solve_env_init(hipStream_t st, int nsub, const SubDesc* gsub, int32_t* F8);
 // Ps.sperm (filled with -1 first) from the chosen layouts (ssub.spare set:
 // global order)
 void launch_solve_perm(hipStream_t st, int nsub, const DevPlan& P, const SubDesc* ssub,
@@ -231,21 +246,33 @@ void launch_solve_perm(hipStream_t st, int nsub, const DevPlan& P, const SubDesc
 void launch_gather_solve(hipStream_t st, int nsub, const DevPlan& P, const DevPlan& Ps,
                          const double* fac, double* out);
 void launch_to_float(hipStream_t st, int64_t n, const double* src, float* dst);
-void launch_gather_local(hipStream_t st, int nsub, const DevPlan& P, const double* scale,
-                         const double* r, double* loc);
-void launch_local_solve(hipStream_t st, int nsub, const DevPlan& P, const double* fac,
-                        const double* dinv, double* loc);
-void launch_local_solve_f32(hipStream_t st, int nsub, const DevPlan& P, const float* fac,
-                            const float* dinv, double* loc);
+// the layout of the chosen solve factor on the device: tile counts of the
+// global-order layouts (tiles[i]) from the envelope F8, then the envelope
+// tables of the layouts ssub (spare set: global order)
+void launch_layout_count(hipStream_t st, int nsub, const SubDesc* gsub, const int32_t* F8, int32_t* tiles);
+void launch_layout_fill(hipStream_t st, int nsub, const DevPlan& P, const SubDesc* ssub,
+                        const SubDesc* gsub, const int32_t* F8, int32_t* tileF, int64_t* tileOff);
+// streams of the layout P (tiles: its stored tiles; F8 and gsub as above, for
+// subdomains with spare set): tables, gather maps, entries
+void launch_stream_layout(hipStream_t st, int nsub, const DevPlan& P, const int32_t* F8,
+                          const SubDesc* gsub, int64_t tiles, const SolveStream& S);
+void launch_solve_cols(hipStream_t st, int nsub, const DevPlan& P, const DevPlan& Lay,
+                       const double* scale, const SolveStream& S);
+template <typename T>
+void launch_stream_pack(hipStream_t st, int nsub, const DevPlan& P, const T* fac, const T* dinv,
+                        const SolveStream& S);
+// loc = S C_ii^{-1} S R_i r for every subdomain (S the equilibration)
+template <typename T>
+void launch_local_solve(hipStream_t st, int nsub, const DevPlan& P, const SolveStream& S, const T* fac,
+                        const T* dinv, const double* r, double* loc);
+int local_solve_cap();    // largest subdomain whose local vector is held in LDS
 // allows the streaming local solve its dynamic LDS (once per process)
 hipError_t local_solve_configure();
 // restricted: each column takes its owner's interior value only (R_i^T D_i, eq. RAS)
-void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* scale,
-                          const double* loc, const double* X, const double* dcoarse, double* z,
-                          bool restricted = false);
-void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* scale,
-                          const double* loc, const float* X, const double* dcoarse, double* z,
-                          bool restricted = false);
+void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* loc,
+                          const double* X, const double* dcoarse, double* z, bool restricted = false);
+void launch_scatter_local(hipStream_t st, int32_t n, const DevPlan& P, const double* loc,
+                          const float* X, const double* dcoarse, double* z, bool restricted = false);
 // ||C(Omega_Ii, :)||_F^2 of every subdomain from the assembled (unscaled) C_ii
 void launch_frob_interior(hipStream_t st, int nsub, const DevPlan& P, const double* fac,
                           double* out);

@@ -25,7 +25,8 @@ void spmv_A(lsq2l_ctx* c, const double* x, double* y);
 void spmv_AT(lsq2l_ctx* c, const double* y, double* x);
 void apply_C(lsq2l_ctx* c, const double* x, double* y, double* tmp);
 void apply_M(lsq2l_ctx* c, const double* r, double* z);
-void local_solves(lsq2l_ctx* c);
+// loc = S_i C_ii^{-1} S_i R_i r of every subdomain
+void local_solves(lsq2l_ctx* c, const double* r);
 // a reduction over the columns or rows of every instance that takes step op
 Reduction reduction(lsq2l_ctx* c, int op, double tol = 0.0);
 void dot(lsq2l_ctx* c, const Segments& G, const double* a, const double* b, const Reduction& R);
