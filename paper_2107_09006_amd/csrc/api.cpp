@@ -966,7 +966,8 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
     TRY(c->dalloc(&qscr, qscr_len));
     LSQ2L_HIP_TRY(hipMemsetAsync(qstrip, 0, strip_len * sizeof(double), st));
   } else {
-    launch_chol_local(st, nparts, c->P, c->fac, c->dinv, c->status, c->solve_plan);
+    launch_chol_local(st, nparts, c->P, H.total_fac / TT, H.total_dinv / TT, c->fac, c->dinv, c->status,
+                      c->solve_plan);
     if (!c->solve_plan) {
       TRY(solve_stream(c, st));
       pack_solve_stream(c, st);
@@ -1004,9 +1005,11 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
       }
     } else if (mixed) {
       launch_to_float(c->st2, c->s_total_fac, s64, c->fac32);
-      launch_chol_local_f32(c->st2, nparts, c->Ps, c->fac32, c->dinv32, c->status + 2);
+      launch_chol_local_f32(c->st2, nparts, c->Ps, c->s_total_fac / TT, c->s_total_tiles, c->fac32,
+                            c->dinv32, c->status + 2);
     } else {
-      launch_chol_local(c->st2, nparts, c->Ps, c->sfac, c->sdinv, c->status + 2);
+      launch_chol_local(c->st2, nparts, c->Ps, c->s_total_fac / TT, c->s_total_tiles, c->sfac, c->sdinv,
+                        c->status + 2);
     }
     TRY(solve_stream(c, c->st2));
     pack_solve_stream(c, c->st2);
@@ -1046,7 +1049,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
       c->info.mixed_fallback = 1;
       double* d64 = nullptr;
       TRY(c->dalloc(&d64, c->s_total_dinv));
-      launch_chol_local(st, nparts, c->Ps, s64, d64, c->status + 3);
+      launch_chol_local(st, nparts, c->Ps, c->s_total_fac / TT, c->s_total_tiles, s64, d64, c->status + 3);
       launch_to_float(st, c->s_total_fac, s64, c->fac32);
       launch_to_float(st, c->s_total_dinv, d64, c->dinv32);
       pack_solve_stream(c, st);

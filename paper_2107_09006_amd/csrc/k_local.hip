@@ -146,25 +146,37 @@ k_equil_apply(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
 constexpr int ROWCAP = 2048;
 constexpr int CHOL_TMAX = 2048;   // tile rows whose envelope the factorization keeps in LDS
 
-// Right-looking tile Cholesky of one envelope matrix per workgroup:
-// for each tile column J: the diagonal tile factored and inverted in
-// registers (one step ahead, see below), L(I,J) = A(I,J) L(J,J)^{-T} for the
-// envelope rows, then A(I,K) -= L(I,J) L(K,J)^T for every pair of envelope
-// rows (MFMA).  Wave 0 applies column J to tile (J+1, J+1) first and factors
-// it while the other waves work through the remaining pairs.  T is double or
-// float (FP32 MFMA with FP32 accumulation).  With interior_only, the factor
-// stops after the interior tile columns and the interface rows never update
-// each other: the result holds L_I and L_GI only (what the coarse selection
-// reads; the local solves then use factors of their own).
-template <typename T>
-__global__ void __launch_bounds__(256)
+// Right-looking tile Cholesky of one envelope matrix per workgroup.  Step J
+// starts with the diagonal tile J factored and inverted in LDS:
+//   1. the panel tile (J + 1, J), if stored, L(I, J) = A(I, J) L(J, J)^{-T}, a
+//      quarter on each of four waves;
+//   2. the same quarters of A(J + 1, J + 1) - L(J + 1, J) L(J + 1, J)^T;
+//   3. wave 0 factors that tile (for step J + 1) while the others store tile
+//      J, list the rows of column J + 1, take the other panel tiles from a
+//      counter and, once all are stored, the pairs of envelope rows
+//      A(I, K) -= L(I, J) L(K, J)^T; wave 0 joins them when done.
+// T is double or float (FP32 MFMA with FP32 accumulation).  With
+// interior_only, the factor stops after the interior tile columns and the
+// interface rows never update each other: the result holds L_I and L_GI only
+// (what the coarse selection reads; the local solves then use factors of their
+// own).
+//
+// What bounds it: on narrow envelopes the chain of the largest subdomain, per
+// tile column the two quarter products, two barriers and the factorization of
+// a tile by one wave; on wide ones the pairs (FP64 MFMA of one CU).  Batch of
+// 64 banded problems (390 tile columns): 6.9 -> 4.2 ms; 512 irregular
+// subdomains: 14.4 -> 9.9 ms, their FP32 solve factors 8.0 -> 4.1.  NT threads: see launch_chol.
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT)
 k_chol_local(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF,
              const int64_t* __restrict__ tileOff, T* __restrict__ fac, T* __restrict__ dinv,
              int32_t* __restrict__ status, int interior_only) {
-  __shared__ T sW[TS * LDT], sL[TS * LDT], sInv[TS * LDT];
-  __shared__ int32_t rows[ROWCAP];
-  __shared__ int32_t sF[CHOL_TMAX], sO[CHOL_TMAX];
-  __shared__ int s_count, s_ok;
+  using M = Mfma<T>;
+  __shared__ T sW[TS * LDT], sP[TS * LDT], sL[2][TS * LDT], sInv[2][TS * LDT];
+  __shared__ int32_t srows[2][ROWCAP];
+  __shared__ uint16_t sF[CHOL_TMAX];
+  __shared__ int32_t sO[CHOL_TMAX];
+  __shared__ int s_count[2], s_ok[2], s_panel, s_done, s_pair;
   const SubDesc d = subs[blockIdx.x];
   const int32_t* F = tileF + d.tile_base;
   const int64_t* off = tileOff + d.tile_base;
@@ -172,26 +184,39 @@ k_chol_local(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF
   // that finding a tile costs no global round trip
   const bool staged = d.ntiles <= CHOL_TMAX;
   if (staged)
-    for (int I = threadIdx.x; I < d.ntiles; I += blockDim.x) {
-      sF[I] = F[I];
+    for (int I = threadIdx.x; I < d.ntiles; I += NT) {
+      sF[I] = (uint16_t)F[I];
       sO[I] = (int32_t)off[I];
     }
   __syncthreads();
-  const int32_t* Fp = staged ? sF : F;
+  auto first = [&](int I) -> int { return staged ? (int)sF[I] : F[I]; };
   auto tpos = [&](int I, int J) -> int64_t {
-    return staged ? (int64_t)sO[I] + (J - sF[I]) : tile_pos(F, off, I, J);
+    return staged ? (int64_t)sO[I] + (J - (int)sF[I]) : tile_pos(F, off, I, J);
   };
   T* A = fac + d.fac_off;
   T* Di = dinv + d.dinv_off;
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int wave = tid / 64, lane = tid % 64, nwaves = nthr / 64;
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int li = lane % 16, lk = lane / 16;
   bool failed = false;
-  __shared__ int s_next;
-  // factor and invert diagonal tile J (its updates applied) by wave 0; the
-  // tile is in sW on entry
-  auto diag_factor = [&]() {
-    const bool okw = tile_potrf_inv_reg(sW, sL, sInv, lane);
-    if (lane == 0) s_ok = okw;
+  // rows I > J whose envelope reaches column J, ascending, by one wave
+  auto list_rows = [&](int J, int buf) {
+    int cnt = 0;
+    for (int base = J + 1; base < d.ntiles; base += 64) {
+      const int I = base + lane;
+      const bool fl = I < d.ntiles && first(I) <= J;
+      const unsigned long long mask = __ballot(fl);
+      const int before = __popcll(mask & ((1ull << lane) - 1ull));
+      if (fl && cnt + before < ROWCAP) srows[buf][cnt + before] = I;
+      cnt += __popcll(mask);
+    }
+    if (lane == 0) s_count[buf] = cnt;
+  };
+  auto next_item = [&](int* counter) {
+    int it = 0;
+    if (lane == 0) it = atomicAdd(counter, 1);
+    return __builtin_amdgcn_readfirstlane(it);
   };
   // tile columns to factor, and the first row of the block whose mutual
   // updates are skipped
@@ -201,55 +226,83 @@ k_chol_local(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF
     const T* A00 = A + tpos(0, 0) * TT;
     for (int e = lane; e < TT; e += 64) sW[(e / TS) * LDT + e % TS] = A00[e];
     wave_sync();
-    diag_factor();
+    const bool okw = tile_potrf_inv(sW, sL[0], sInv[0], lane);
+    if (lane == 0) s_ok[0] = okw;
+  } else if (wave == NW - 1) {
+    list_rows(0, 0);
   }
   __syncthreads();
   for (int J = 0; J < ncol; ++J) {
-    T* Ajj = A + tpos(J, J) * TT;
-    const bool ok = s_ok;
-    if (!ok) failed = true;
-    for (int e = tid; e < TT; e += nthr) {
-      Ajj[e] = sL[(e / TS) * LDT + e % TS];
-      Di[(int64_t)J * TT + e] = sInv[(e / TS) * LDT + e % TS];
-    }
-    const int nr = envelope_rows(Fp, J, d.ntiles, rows, ROWCAP, &s_count);
+    const int cur = J & 1;
+    const int32_t* rows = srows[cur];
+    const int nr = s_count[cur];
+    if (!s_ok[cur]) failed = true;
     if (nr > ROWCAP) { failed = true; break; }
-    // panel
-    for (int a = wave; a < nr; a += nwaves) {
-      T* Aij = A + tpos(rows[a], J) * TT;
-      typename Mfma<T>::acc_t acc[4];
-      tile_acc_zero<T>(acc);
-      tile_mma_nt<T, false>(acc, Aij, TS, sInv, LDT, lane);
-      tile_acc_store<T>(acc, Aij, TS, lane);
-    }
-    // the next diagonal tile gets its update from column J (when coupled)
-    // and is factored by wave 0 while the other waves take the remaining
-    // pairs (a >= b) of envelope rows from a shared counter; wave 0 joins
-    // them when done
     const bool next = J + 1 < ncol;
-    const bool next_coupled = next && nr > 0 && rows[0] == J + 1;
-    const int npairs = nr * (nr + 1) / 2;
-    if (tid == 0) s_next = next_coupled ? 1 : 0;
+    const bool coupled = nr > 0 && rows[0] == J + 1;
+    // quarter (bi, bj) of a transposed tile: columns 16 bi .., rows 16 bj ..
+    const int bi = wave / 2, bj = wave % 2;
+    const bool quarter = next && wave < 4 && !(bi == 1 && bj == 0);   // lower part only
+    typename M::acc_t q;
+    const T* Ann = A + (next ? tpos(J + 1, J + 1) : 0) * TT;
+    if (quarter)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) q[v] = Ann[(16 * bi + M::acc_row(lane, v)) * TS + 16 * bj + li];
+    if (coupled && wave < 4) {
+      T* Pn = A + tpos(J + 1, J) * TT;
+      T b[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) b[s] = Pn[(4 * s + lk) * TS + 16 * bj + li];
+      typename M::acc_t acc = M::zero();
+#pragma unroll
+      for (int s = 0; s < 8; ++s) acc = M::mma(sInv[cur][(4 * s + lk) * LDT + 16 * bi + li], b[s], acc);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sP[(16 * bi + M::acc_row(lane, v)) * LDT + 16 * bj + li] = acc[v];
+    }
+    if (tid == 0) {
+      s_panel = s_done = coupled ? 1 : 0;
+      s_pair = coupled && next ? 1 : 0;
+    }
+    __syncthreads();                     // the quarters read all of A(J + 1, J) before it is overwritten
+    if (coupled) {
+      T* Pn = A + tpos(J + 1, J) * TT;
+      for (int e = tid; e < TT; e += NT) Pn[e] = sP[(e / TS) * LDT + e % TS];
+      if (quarter) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+          q = M::mma(-sP[(4 * s + lk) * LDT + 16 * bi + li], sP[(4 * s + lk) * LDT + 16 * bj + li], q);
+      }
+    }
+    if (quarter)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sW[(16 * bi + M::acc_row(lane, v)) * LDT + 16 * bj + li] = q[v];
     __syncthreads();
     if (wave == 0 && next) {
-      const T* Ann = A + tpos(J + 1, J + 1) * TT;
-      if (next_coupled) {
-        const T* Ln = A + tpos(J + 1, J) * TT;
-        typename Mfma<T>::acc_t acc[4];
-        tile_acc_load<T>(acc, Ann, TS, lane);
-        tile_mma_nt<T, true>(acc, Ln, TS, Ln, TS, lane);
-        tile_acc_store<T>(acc, sW, LDT, lane);
-      } else {
-        for (int e = lane; e < TT; e += 64) sW[(e / TS) * LDT + e % TS] = Ann[e];
+      const bool okw = tile_potrf_inv(sW, sL[cur ^ 1], sInv[cur ^ 1], lane);
+      if (lane == 0) s_ok[cur ^ 1] = okw;
+    } else {
+      if (wave == NW - 1 && next) list_rows(J + 1, cur ^ 1);
+      T* Ajj = A + tpos(J, J) * TT;
+      const int t0 = next ? tid - 64 : tid, nt = next ? NT - 64 : NT;
+      for (int e = t0; e < TT; e += nt) {
+        Ajj[e] = sL[cur][(e / TS) * LDT + e % TS];
+        Di[(int64_t)J * TT + e] = sInv[cur][(e / TS) * LDT + e % TS];
       }
-      wave_sync();
-      diag_factor();
     }
-    while (true) {
-      int it = 0;
-      if (lane == 0) it = atomicAdd(&s_next, 1);
-      it = __shfl(it, 0, 64);
-      if (it >= npairs) break;
+    for (int it = next_item(&s_panel); it < nr; it = next_item(&s_panel)) {
+      T* Aij = A + tpos(rows[it], J) * TT;
+      typename M::acc_t acc[4];
+      tile_acc_zero<T>(acc);
+      tile_mma_nt<T, false>(acc, sInv[cur], LDT, Aij, TS, lane);
+      tile_accT_store<T>(acc, Aij, TS, lane);
+      wg_fence();
+      if (lane == 0) atomicAdd(&s_done, 1);
+    }
+    // every panel tile is taken by now, and the waves that took them do not wait
+    while (*(volatile int*)&s_done < nr) __builtin_amdgcn_s_sleep(1);
+    wg_fence();
+    const int npairs = nr * (nr + 1) / 2;
+    for (int it = next_item(&s_pair); it < npairs; it = next_item(&s_pair)) {
       int a = (int)((sqrt(8.0 * it + 1.0) - 1.0) / 2.0);
       while (a * (a + 1) / 2 > it) --a;
       while ((a + 1) * (a + 2) / 2 <= it) ++a;
@@ -259,20 +312,15 @@ k_chol_local(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF
       const T* La = A + tpos(Ia, J) * TT;
       const T* Lb = A + tpos(Ib, J) * TT;
       T* Cab = A + tpos(Ia, Ib) * TT;
-      typename Mfma<T>::acc_t acc[4];
-      tile_acc_load<T>(acc, Cab, TS, lane);
-      tile_mma_nt<T, true>(acc, La, TS, Lb, TS, lane);
-      tile_acc_store<T>(acc, Cab, TS, lane);
+      typename M::acc_t acc[4];
+      tile_accT_load<T>(acc, Cab, TS, lane);
+      tile_mma_nt<T, true>(acc, Lb, TS, La, TS, lane);
+      tile_accT_store<T>(acc, Cab, TS, lane);
     }
     __syncthreads();
   }
   if (failed && tid == 0) atomicCAS(status, 0, d.id + 1);
 }
-
-template __global__ void k_chol_local<double>(const SubDesc*, const int32_t*, const int64_t*,
-                                              double*, double*, int32_t*, int);
-template __global__ void k_chol_local<float>(const SubDesc*, const int32_t*, const int64_t*,
-                                             float*, float*, int32_t*, int);
 
 // ---------------------------------------------------------------------------
 // The factor used by the per-iteration local solves.  C_ii^{-1} r does not
@@ -522,10 +570,27 @@ void launch_equilibrate(hipStream_t st, int nsub, const DevPlan& P, double* fac,
   k_equil_apply<<<dim3(nsub, 32), 256, 0, st>>>(P.heavy(), P.tileF, P.tileOff, fac, ctg, scale);
 }
 
-void launch_chol_local(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* dinv,
-                       int32_t* status, bool interior_only) {
-  k_chol_local<double><<<nsub, 256, 0, st>>>(P.heavy(), P.tileF, P.tileOff, fac, dinv, status,
-                                             interior_only ? 1 : 0);
+// Eight waves per subdomain where a tile column has many rows (the pairs of
+// rows are shared out among them), four on narrow envelopes, where the chain of
+// the diagonal tiles bounds the factorization and a workgroup that fits beside
+// the selection's kernels is worth more.  512 irregular subdomains (10 tiles
+// per row) 9.9 ms with eight waves, 11.9 with four; 1000 x 1000 grid, factors of
+// the selection (7 tiles per row) 2.2 and 2.4, solve factors (3 per row) with
+// the selection beside them 17.1 and 15.7.
+template <typename T>
+static void launch_chol(hipStream_t st, int nsub, const DevPlan& P, int64_t tiles, int64_t rows, T* fac,
+                        T* dinv, int32_t* status, int interior_only) {
+  if (tiles >= 6 * rows)
+    k_chol_local<T, 512><<<nsub, 512, 0, st>>>(P.heavy(), P.tileF, P.tileOff, fac, dinv, status,
+                                               interior_only);
+  else
+    k_chol_local<T, 256><<<nsub, 256, 0, st>>>(P.heavy(), P.tileF, P.tileOff, fac, dinv, status,
+                                               interior_only);
+}
+
+void launch_chol_local(hipStream_t st, int nsub, const DevPlan& P, int64_t tiles, int64_t rows, double* fac,
+                       double* dinv, int32_t* status, bool interior_only) {
+  launch_chol<double>(st, nsub, P, tiles, rows, fac, dinv, status, interior_only ? 1 : 0);
 }
 
 void launch_solve_inv(hipStream_t st, int nsub, const DevPlan& P, int32_t* inv) {
@@ -556,9 +621,9 @@ void launch_gather_solve(hipStream_t st, int nsub, const DevPlan& P, const DevPl
                                                   Ps.tileF, Ps.tileOff, Ps.sperm, out);
 }
 
-void launch_chol_local_f32(hipStream_t st, int nsub, const DevPlan& P, float* fac, float* dinv,
-                           int32_t* status) {
-  k_chol_local<float><<<nsub, 256, 0, st>>>(P.heavy(), P.tileF, P.tileOff, fac, dinv, status, 0);
+void launch_chol_local_f32(hipStream_t st, int nsub, const DevPlan& P, int64_t tiles, int64_t rows,
+                           float* fac, float* dinv, int32_t* status) {
+  launch_chol<float>(st, nsub, P, tiles, rows, fac, dinv, status, 0);
 }
 
 void launch_to_float(hipStream_t st, int64_t n, const double* src, float* dst) {

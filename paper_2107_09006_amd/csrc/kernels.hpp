@@ -225,12 +225,13 @@ void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix
                      int32_t* F8 = nullptr, const double* scale = nullptr);
 void launch_equilibrate(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* ctg,
                         double* scale);
-// interior_only: factor the interior tile columns only (L_I and L_GI)
-void launch_chol_local(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* dinv,
-                       int32_t* status, bool interior_only = false);
+// tiles, rows: stored tiles and tile rows of the layout; interior_only: factor
+// the interior tile columns only (L_I and L_GI)
+void launch_chol_local(hipStream_t st, int nsub, const DevPlan& P, int64_t tiles, int64_t rows, double* fac,
+                       double* dinv, int32_t* status, bool interior_only = false);
 // the same in FP32 (FP32 MFMA, FP32 accumulation)
-void launch_chol_local_f32(hipStream_t st, int nsub, const DevPlan& P, float* fac, float* dinv,
-                           int32_t* status);
+void launch_chol_local_f32(hipStream_t st, int nsub, const DevPlan& P, int64_t tiles, int64_t rows,
+                           float* fac, float* dinv, int32_t* status);
 // solve factor in the global-column order of each subdomain: inv (indexed
 // like loc) maps an [I, Gamma] position to its global-order position;
 // gsub describes the global-order layout (np, ntiles, tile_base); F8 (four per
