@@ -891,25 +891,33 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
   TRY(c->dalloc(&c->ctg, H.total_g));
   TRY(c->dalloc(&c->status, 8));
   LSQ2L_HIP_TRY(hipMemsetAsync(c->status, 0, 8 * sizeof(int32_t), st));
-  LSQ2L_HIP_TRY(hipMemsetAsync(c->fac, 0, H.total_fac * sizeof(double), st));
+  // the QR factors are merged into a cleared array; the assembly writes all of it
+  if (c->opt.local_factor == LSQ2L_FACTOR_QR)
+    LSQ2L_HIP_TRY(hipMemsetAsync(c->fac, 0, H.total_fac * sizeof(double), st));
   if (H.total_g) LSQ2L_HIP_TRY(hipMemsetAsync(c->ctg, 0, H.total_g * sizeof(double), st));
   TRY(solve_layout_begin(c));
+  int2* owner = nullptr;
+  TRY(c->dalloc(&owner, nnz));
+  launch_entry_owner(st, c->P, c->M, owner);
   const bool qr = c->opt.local_factor == LSQ2L_FACTOR_QR;
   if (qr) {
     // QR local factors (Remarks 3.1, 3.2): no C_ii is formed.  The pattern
     // pass of the assembly still gives the envelope of the global-order
     // layouts; the equilibration's scaling comes from the column norms of A.
-    if (c->sl_inv) launch_assemble(st, nparts, c->P, c->M, nullptr, nullptr, c->sl_inv, c->sl_dg, c->sl_F8);
+    if (c->sl_inv)
+      launch_assemble(st, nparts, c->P, c->M, owner, nullptr, nullptr, c->sl_inv, c->sl_dg,
+                      c->sl_F8, nullptr);
     launch_col_scale(st, nparts, c->P, c->M, c->scale);
   } else if (c->opt.diag_shift_rel <= 0.0) {
     // S = diag(C_ii)^{-1/2} = 1 / ||A(:, c)|| first, then S C_ii S and
     // S Ct_GG S assembled in one pass
     c->shift = 0.0;
     launch_col_scale(st, nparts, c->P, c->M, c->scale);
-    launch_assemble(st, nparts, c->P, c->M, c->fac, c->ctg, c->sl_inv, c->sl_dg, c->sl_F8,
-                    c->scale);
+    launch_assemble(st, nparts, c->P, c->M, owner, c->fac, c->ctg, c->sl_inv, c->sl_dg,
+                    c->sl_F8, c->scale);
   } else {
-  launch_assemble(st, nparts, c->P, c->M, c->fac, c->ctg, c->sl_inv, c->sl_dg, c->sl_F8);
+  launch_assemble(st, nparts, c->P, c->M, owner, c->fac, c->ctg, c->sl_inv, c->sl_dg,
+                  c->sl_F8, nullptr);
   // Global shift of Section 4.1 ("Setup phase"): the preconditioner is built
   // for C + s I, s = diag_shift_rel ||C||_F, i.e. for the least-squares
   // matrix [A; sqrt(s) I].  Its rows sqrt(s) e_j enter Xi_i for j in

@@ -15,30 +15,44 @@
 
 namespace lsq2l {
 
-__global__ void k_gather_values(int64_t nnz, const int32_t* __restrict__ perm,
-                                const double* __restrict__ src, double* __restrict__ dst) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < nnz) dst[k] = src[perm[k]];
+// owner[e] = (part[c], locown[c]) of the column c of entry e
+__global__ void k_entry_owner(int64_t nnz, const int32_t* __restrict__ colind, const int32_t* __restrict__ part,
+                              const int32_t* __restrict__ locown, int2* __restrict__ owner) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= nnz) return;
+  const int c = colind[e];
+  owner[e] = int2{part[c], locown[c]};
 }
 
-// Lower triangle of C_ii (tile-envelope layout) and of Ct_GG (dense, ld nGp);
-// with fac null, only the envelope F8 below.
-// Thread per local column: every write of a thread lands in its own column,
-// so the accumulation order is fixed and no atomics are needed.  Workgroup
-// (i, y) takes the columns y * 256 + t, (y + gridDim.y) * 256 + t, ... of
-// subdomain i, so that a large subdomain spreads over several compute units.
-// With inv given, it also finds the tile envelope of C_ii in the global
-// column order (see k_solve_inv): the thread of column a sees every column
-// coupled to it, so the first coupled position of row inv[a] in that order
-// is the minimum it meets, one atomicMin per column into F8 (one entry per
-// eight rows).
+// Lower triangle of C_ii (tile-envelope layout) and of Ct_GG (dense, ld nGp).
+// Workgroup (i, y) takes the tile columns y, y + gridDim.y, ... of subdomain i,
+// a wave CPW columns at a time: LPR lanes walk the entries of each row of A that
+// holds the column, and every product is added in LDS at its row's place among
+// the column's stored tiles (one wave's adds, in a fixed order).  The
+// finished column is written once, zeros included, so the factor array needs
+// no clearing.  Columns with more than NTL stored tiles take several passes over
+// their rows.  owner[e] = (part, local position there) of the column of entry e,
+// gathered once for all subdomains.
+// With inv given, it also finds the envelope of C_ii in the global column order
+// (see k_solve_inv): the wave of column a sees every column coupled to it, so
+// the first coupled position of row inv[a] in that order is the minimum it
+// meets, one atomicMin per column into F8 (one entry per eight rows).  With
+// fac null that envelope is all it finds.
 // With scl given (S = diag(C_ii)^{-1/2} per local position, which is
-// 1 / ||A(:, c)||: C_ii holds whole columns of A), every product is scaled as
-// it is added, so the result is S C_ii S and S Ct_GG S directly, with unit
-// diagonal entries on the padding positions (the equilibration in one pass).
+// 1 / ||A(:, c)||: C_ii holds whole columns of A), the result is S C_ii S and
+// S Ct_GG S, with unit diagonal entries on the padding positions (the
+// equilibration in one pass).
+//
+// What bounds it: the look-ups of the entries' positions and the factor array
+// written once.  One thread per column, adding every product to its place in
+// memory, took 14.7 ms (irregular, 1e6 columns, 4 GB of tiles, cleared before
+// in 1.0) and 4.4 (batch of 3e6 columns, 3 GB); this takes 5.2 and 2.6.
+constexpr int ASM_G = 1024;       // interface columns held in LDS
+constexpr int ASM_MAP = 4096;     // tile rows with a direct slot table
+template <int NTL, int CPW, int LPR>
 __global__ void __launch_bounds__(256)
 k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
-           const int32_t* __restrict__ part, const int32_t* __restrict__ locown,
+           const int2* __restrict__ owner,
            const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
            const double* __restrict__ vals, const int32_t* __restrict__ trowptr,
            const int32_t* __restrict__ trow, const double* __restrict__ tvals,
@@ -46,46 +60,167 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
            double* __restrict__ fac, double* __restrict__ ctg, const int32_t* __restrict__ inv,
            const SubDesc* __restrict__ gsub, int32_t* __restrict__ F8,
            const double* __restrict__ scl) {
+  __shared__ __align__(16) double sAcc[4][CPW * NTL * TS];
+  constexpr int SW = 64 / CPW;      // lanes of a column
+  __shared__ int32_t sG[ASM_G], sList[NTL];
+  __shared__ int64_t sBase[NTL];                // the stored tiles' places in A
+  __shared__ __align__(16) double sScl[NTL * TS];             // S of their rows
+  __shared__ uint8_t sMap[ASM_MAP];
+  __shared__ int s_cnt, s_next;
   const SubDesc d = subs[blockIdx.x];
-  const int i = d.id;
+  const int i = d.id, tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const double* sl = scl ? scl + d.loc_off : nullptr;
   const int32_t* iv = inv ? inv + d.loc_off : nullptr;
   const int32_t* om = omega + d.omega_off;
   const int32_t* G = om + d.nI;
   const int32_t* F = tileF + d.tile_base;
   const int64_t* off = tileOff + d.tile_base;
-  double* A = fac ? fac + d.fac_off : nullptr;    // null: the envelope Fg only
+  double* A = fac ? fac + d.fac_off : nullptr;
   double* Ct = ctg ? ctg + d.g_off : nullptr;
-  for (int a = blockIdx.y * blockDim.x + threadIdx.x; a < d.nI + d.nG; a += gridDim.y * blockDim.x) {
-    const int j = om[a];
-    const int posa = a < d.nI ? a : d.nIp + (a - d.nI);
-    const int ta = posa / TS, ra = posa % TS;
-    const int qa = iv ? iv[posa] : 0;
-    const double sa = sl ? sl[posa] : 1.0;
-    int fmin = qa;
-    for (int k = trowptr[j]; k < trowptr[j + 1]; ++k) {
-      const int r = trow[k];
-      const double va = tvals[k];
-      const int e0 = rowptr[r], e1 = rowptr[r + 1];
-      bool inxi = false;
-      if (A) for (int e = e0; e < e1; ++e) inxi |= (part[colind[e]] == i);
-      for (int e = e0; e < e1; ++e) {
-        const int posc = local_pos(i, colind[e], part, locown, G, d.nG, d.nIp);
-        if (iv && posc >= 0) fmin = min(fmin, iv[posc]);
-        if (!A || posc < posa) continue;
-        const double v = sl ? vals[e] * va * (sa * sl[posc]) : vals[e] * va;
-        const int tc = posc / TS;
-        A[tile_pos(F, off, tc, ta) * TT + ra * TS + (posc % TS)] += v;
-        if (inxi && a >= d.nI) Ct[(int64_t)(posa - d.nIp) * d.nGp + (posc - d.nIp)] += v;
+  double* acc = sAcc[wave];
+  const bool gl = d.nG <= ASM_G, map = d.ntiles <= ASM_MAP;
+  if (gl)
+    for (int q = tid; q < d.nG; q += 256) sG[q] = G[q];
+  if (map)
+    for (int q = tid; q < d.ntiles; q += 256) sMap[q] = 255;
+  for (int q = lane; q < CPW * NTL * TS; q += 64) acc[q] = 0.0;
+  __syncthreads();
+  // local position of global column c owned by w, or -1
+  auto position = [&](int c, int2 w) -> int {
+    if (w.x == i) return w.y;
+    int lo = 0, hi = d.nG;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if ((gl ? sG[mid] : G[mid]) < c) lo = mid + 1; else hi = mid;
+    }
+    return lo < d.nG && (gl ? sG[lo] : G[lo]) == c ? d.nIp + lo : -1;
+  };
+  for (int J = blockIdx.y; J < d.ntiles; J += gridDim.y) {
+    int I0 = J;
+    while (I0 < d.ntiles) {
+      // the next (at most NTL) stored tiles of this tile column
+      if (wave == 0) {
+        int cnt = 0, at = I0;
+        if (A) {
+          while (at < d.ntiles && cnt < NTL) {
+            const int I = at + lane;
+            const bool fl = I < d.ntiles && F[I] <= J;
+            const unsigned long long m = __ballot(fl);
+            const int before = __popcll(m & ((1ull << lane) - 1ull));
+            const bool take = fl && cnt + before < NTL;
+            if (take) {
+              sList[cnt + before] = I;
+              if (map) sMap[I] = (uint8_t)(cnt + before);
+            }
+            const unsigned long long tk = __ballot(take);
+            cnt += __popcll(tk);
+            at += 64;
+            if (tk != m) break;
+          }
+          wave_sync();
+          if (cnt == NTL) at = sList[NTL - 1] + 1;   // a full list: resume after its last row
+        } else {
+          at = d.ntiles;
+        }
+        if (lane == 0) { s_cnt = cnt; s_next = at; }
       }
+      __syncthreads();
+      const int cnt = s_cnt, nextI = s_next;
+      for (int q = tid; q < cnt; q += 256) sBase[q] = tile_pos(F, off, sList[q], J) * TT;
+      if (sl)
+        for (int q = tid; q < cnt * TS; q += 256) sScl[q] = sl[sList[q / TS] * TS + q % TS];
+      __syncthreads();
+      auto slot = [&](int I) -> int {
+        if (map) return sMap[I] == 255 ? -1 : (int)sMap[I];
+        int lo = 0, hi = cnt;
+        while (lo < hi) {
+          const int mid = (lo + hi) >> 1;
+          if (sList[mid] < I) lo = mid + 1; else hi = mid;
+        }
+        return lo < cnt && sList[lo] == I ? lo : -1;
+      };
+      // column of group t and place u; lane t CPW + u holds the extent of its rows
+      auto column = [&](int t, int u) { return J * TS + (4 * t + wave) * CPW + u; };
+      int ext0 = 0, ext1 = 0;
+      if (lane < TS / 4) {
+        const int pos = column(lane / CPW, lane % CPW);
+        const int at = pos < d.nI ? pos : pos >= d.nIp && pos < d.nIp + d.nG ? d.nI + pos - d.nIp : -1;
+        if (at >= 0) {
+          ext0 = trowptr[om[at]];
+          ext1 = trowptr[om[at] + 1];
+        }
+      }
+      const bool interior = J < d.ntI;                   // the whole tile column
+      const int npass = !interior && Ct ? 2 : 1;         // C_ii, then Ct_GG (rows in Xi_i)
+      for (int t = 0; t < TS / (4 * CPW); ++t) {
+        const int u = lane / SW, pos = column(t, u);
+        const int k0 = __shfl(ext0, t * CPW + u, 64), k1 = __shfl(ext1, t * CPW + u, 64);
+        const bool real = k0 < k1;                       // every column of Omega_i has an entry
+        double* mine = acc + u * (NTL * TS);
+        for (int pass = 0; pass < npass; ++pass) {
+          const int qa = iv && real ? iv[pos] : 0;
+          int fmin = qa;
+          for (int k = k0 + lane % SW / LPR; k < k1; k += SW / LPR) {
+            const int r = trow[k];
+            const double va = tvals[k];
+            const int e0 = rowptr[r], e1 = rowptr[r + 1];
+            bool inxi = true;
+            if (pass == 1) {
+              inxi = false;
+              for (int e = e0 + lane % LPR; e < e1; e += LPR) inxi |= owner[e].x == i;
+              const unsigned long long m = __ballot(inxi);
+              inxi = (m >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1ull);
+            }
+            if (!inxi) continue;
+            for (int e = e0 + lane % LPR; e < e1; e += LPR) {
+              const double v = vals[e];
+              const int pc = position(colind[e], owner[e]);
+              if (pc < 0) continue;
+              if (iv) fmin = min(fmin, iv[pc]);
+              if (!A || pc < pos) continue;
+              const int sI = slot(pc / TS);
+              if (sI >= 0) __builtin_amdgcn_ds_atomic_fadd_f64(
+                  (__attribute__((address_space(3))) double*)(mine + sI * TS + pc % TS), v * va);
+            }
+          }
+          if (iv && pass == 0 && I0 == J) {
+#pragma unroll
+            for (int o = SW / 2; o > 0; o >>= 1) fmin = min(fmin, __shfl_xor(fmin, o, 64));
+            if (real && lane % SW == 0) atomicMin(&F8[4 * gsub[i].tile_base + qa / 8], fmin);
+          }
+          wave_sync();
+#pragma unroll
+          for (int w = 0; w < CPW; ++w) {
+            const int pw = column(t, w);
+            const bool rw = pw < d.nI || (pw >= d.nIp && pw < d.nIp + d.nG);
+            const double sa = sl ? sl[pw] : 1.0;
+            double* from = acc + w * (NTL * TS);
+            for (int s = lane / (TS / 2); s < cnt; s += 128 / TS) {
+              const int rr = lane % (TS / 2) * 2, row = sList[s] * TS + rr;
+              double2* at = reinterpret_cast<double2*>(from + s * TS + rr);
+              double2 v = *at;
+              *at = double2{0.0, 0.0};
+              if (sl) {
+                const double2 sr = *reinterpret_cast<const double2*>(sScl + s * TS + rr);
+                v.x = !rw && row == pw ? 1.0 : v.x * (sa * sr.x);
+                v.y = !rw && row + 1 == pw ? 1.0 : v.y * (sa * sr.y);
+              }
+              if (pass == 0) *reinterpret_cast<double2*>(A + sBase[s] + (pw - J * TS) * TS + rr) = v;
+              else if (row >= d.nIp)
+                *reinterpret_cast<double2*>(Ct + (int64_t)(pw - d.nIp) * d.nGp + (row - d.nIp)) = v;
+            }
+          }
+          wave_sync();
+        }
+      }
+      __syncthreads();
+      if (map && wave == 0)
+        for (int q = lane; q < cnt; q += 64) sMap[sList[q]] = 255;
+      __syncthreads();
+      I0 = nextI;
     }
-    if (iv) atomicMin(&F8[4 * gsub[i].tile_base + qa / 8], fmin);
   }
-  if (A && sl && blockIdx.y == 0)
-    for (int pos = threadIdx.x; pos < d.np; pos += blockDim.x) {
-      const bool real = pos < d.nI || (pos >= d.nIp && pos < d.nIp + d.nG);
-      if (!real) A[tile_pos(F, off, pos / TS, pos / TS) * TT + (pos % TS) * TS + pos % TS] = 1.0;
-    }
 }
 
 // Symmetric diagonal equilibration S C S, S = diag(C)^{-1/2} (an exact
@@ -547,21 +682,26 @@ __global__ void k_scatter_local(int32_t n, const int32_t* __restrict__ own_ptr,
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-void launch_gather_values(hipStream_t st, int64_t nnz, const int32_t* perm, const double* src,
-                          double* dst) {
-  if (nnz == 0) return;
-  k_gather_values<<<(unsigned)((nnz + 255) / 256), 256, 0, st>>>(nnz, perm, src, dst);
+void launch_entry_owner(hipStream_t st, const DevPlan& P, const DevMatrix& M, int2* owner) {
+  if (M.nnz == 0) return;
+  k_entry_owner<<<(unsigned)((M.nnz + 255) / 256), 256, 0, st>>>(M.nnz, M.colind, P.part, P.locown, owner);
 }
 
-void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, double* fac,
-                     double* ctg, const int32_t* inv, const SubDesc* gsub, int32_t* F8,
+// Rows of up to four entries on average (a grid's edges have two, the banded
+// rows four) fill four lanes each, and two columns at a time hide the loads'
+// latency (batch of 3e6 banded columns 2.6 ms, grid of 1e6 1.0; one column and
+// eight lanes 3.3 and 1.2).  Longer rows take eight lanes, one column and 16
+// slots, for their wider envelopes (irregular, 1e6 columns, rows of 1 to 40:
+// 5.2 ms; two columns and four lanes 7.0).
+void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, const int2* owner,
+                     double* fac, double* ctg, const int32_t* inv, const SubDesc* gsub, int32_t* F8,
                      const double* scale) {
-  // workgroups per subdomain: enough for the largest one to take 2 columns
-  // per thread (at most 64)
-  const int ny = std::max(1, std::min(64, (P.max_np + 511) / 512));
-  k_assemble<<<dim3(nsub, ny), 256, 0, st>>>(P.heavy(), P.omega, P.part, P.locown, M.rowptr,
-                                             M.colind, M.vals, M.trowptr, M.trow, M.tvals, P.tileF,
-                                             P.tileOff, fac, ctg, inv, gsub, F8, scale);
+  // workgroups per subdomain: two tile columns each in a subdomain of 1,024
+  // positions, at most 32
+  const int ny = std::max(1, std::min(32, P.max_np / (2 * TS)));
+  auto* kernel = M.nnz <= 4 * (int64_t)M.m ? k_assemble<8, 2, 4> : k_assemble<16, 1, 8>;
+  kernel<<<dim3(nsub, ny), 256, 0, st>>>(P.heavy(), P.omega, owner, M.rowptr, M.colind, M.vals, M.trowptr,
+                                         M.trow, M.tvals, P.tileF, P.tileOff, fac, ctg, inv, gsub, F8, scale);
 }
 
 void launch_equilibrate(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* ctg,

@@ -214,15 +214,16 @@ void launch_normalize_seg(hipStream_t st, int64_t n, int S, const int64_t* seg_p
                           const double* nrm2, const int32_t* done, const double* a, double* out);
 
 // --- subdomain kernels -------------------------------------------------------
-void launch_gather_values(hipStream_t st, int64_t nnz, const int32_t* perm, const double* src,
-                          double* dst);
 // with inv (not null), also the envelope F8 of the global-order layouts gsub:
 // per eight rows the first position they reach (launch_solve_env_init first)
 // scale non-null: assemble S C_ii S and S Ct_GG S directly (S = scale, from
 // launch_col_scale), identity on the padding diagonal
-void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, double* fac,
-                     double* ctg, const int32_t* inv = nullptr, const SubDesc* gsub = nullptr,
-                     int32_t* F8 = nullptr, const double* scale = nullptr);
+// owner: per entry of A the part and local position of its column
+// (launch_entry_owner); fac need not be cleared
+void launch_entry_owner(hipStream_t st, const DevPlan& P, const DevMatrix& M, int2* owner);
+void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, const int2* owner,
+                     double* fac, double* ctg, const int32_t* inv, const SubDesc* gsub, int32_t* F8,
+                     const double* scale);
 void launch_equilibrate(hipStream_t st, int nsub, const DevPlan& P, double* fac, double* ctg,
                         double* scale);
 // tiles, rows: stored tiles and tile rows of the layout; interior_only: factor
