@@ -259,14 +259,13 @@ __device__ inline float lane_bcast(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// 1 / sqrt(d) and 1 / d from the hardware estimates.  In double (relative
-// error of the estimate e0 below 2^-23) one third-order step,
-// r + r e (1/2 + 3/8 e) with e = 1 - d r^2, and r + r e (1 + e) with
-// e = 1 - d r, leaves e0^3; in float one Newton-Raphson step.
+// 1 / sqrt(d) from the hardware estimate, refined by Newton-Raphson steps
+// r <- r + r (1 - d r^2) / 2 (the error roughly squares each step): two in
+// double, one in float
 __device__ inline double rsqrt_refined(double d) {
-  const double r = __builtin_amdgcn_rsq(d);
-  const double e = fma(-(d * r), r, 1.0);
-  return fma(r * e, fma(0.375, e, 0.5), r);
+  double rs = __builtin_amdgcn_rsq(d);
+  rs = fma(0.5 * rs, fma(-d * rs, rs, 1.0), rs);
+  return fma(0.5 * rs, fma(-d * rs, rs, 1.0), rs);
 }
 
 __device__ inline float rsqrt_refined(float d) {
@@ -274,15 +273,25 @@ __device__ inline float rsqrt_refined(float d) {
   return fmaf(0.5f * rs, fmaf(-d * rs, rs, 1.0f), rs);
 }
 
-__device__ inline double rcp_refined(double d) {
-  const double r = __builtin_amdgcn_rcp(d);
-  const double e = fma(-d, r, 1.0);
-  return fma(r * e, 1.0 + e, r);
+// x of the lanes g * 16 + lane % 16, g = 0 .. 3
+__device__ inline void rows_of_column(int x, int (&r)[4]) {
+  const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  const auto lo = __builtin_amdgcn_permlane16_swap(h[0], h[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(h[1], h[1], false, false);
+  r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
 }
-
-__device__ inline float rcp_refined(float d) {
-  const float r = __builtin_amdgcn_rcpf(d);
-  return fmaf(r, fmaf(-d, r, 1.0f), r);
+__device__ inline void rows_of_column(float x, float (&r)[4]) {
+  int q[4];
+  rows_of_column(__float_as_int(x), q);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) r[g] = __int_as_float(q[g]);
+}
+__device__ inline void rows_of_column(double x, double (&r)[4]) {
+  int lo[4], hi[4];
+  rows_of_column(__double2loint(x), lo);
+  rows_of_column(__double2hiint(x), hi);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) r[g] = __hiloint2double(hi[g], lo[g]);
 }
 
 // L L^T = W and Inv = L^{-1} for one SPD tile W (column-major in LDS, leading
@@ -292,104 +301,133 @@ __device__ inline float rcp_refined(float d) {
 // caller can continue and report).  T is double or float (the arithmetic of the
 // whole tile).
 //
-// The tile (A) and the running inverse (Z) stay in MFMA accumulators whose
-// register v holds rows l / 16 + 4 v of a 16 x 16 block in lane l: a panel's
-// four rows are one register, and that register is already a matrix operand
-// (k = l / 16).  Per panel, the 4 x 4 diagonal block is read by every lane and
-// factored and inverted there; one product with that inverse gives the panel's
-// rows of L^T (P) and of Z, and rank-4 products update A and Z.  In float the
-// accumulator holds rows 4 (l / 16) + v instead, so the rows are given those
-// places (the row operands are permuted within their 16 lanes to match).
-// Bound by the chain of four pivots per panel (a reciprocal each) and 56 MFMAs.  One tile takes 10,100 cycles in
-// double (24,000 with one column per step, read lane by lane) and 6,800 in
-// float.
+// The arithmetic is that of eliminating one column after the other: entry
+// (i, j) is fma(-W(i, k), W(k, j) / d_k, .) for k = 0, 1, ... of both triangles, each
+// rounded by itself, which is what an FP64 MFMA does with four k in a row.
+// So the result has the bits of that elimination: grids whose coarse operator is
+// nearly singular turn a change of rounding here into 1e-8 of M r.
+//
+// The tile stays in MFMA accumulators whose register v holds rows l / 16 + 4 v of
+// a 16 x 16 block in lane l: its upper triangle in A, the transpose of its lower
+// triangle in B, the running inverse in Z.  A panel's four rows are then one
+// register of each, which is already a matrix operand (k = l / 16).  Per panel
+// every lane eliminates the 4 x 4 diagonal block and then, with the four rows of
+// its column gathered across the wave, the panel's rows of A, B and Z; rank-4
+// products update the rest.  In float the accumulator holds rows 4 (l / 16) + v
+// instead, so the rows are given those places (the row operands are permuted
+// within their 16 lanes to match).  Bound by the chain of four pivots per panel
+// (an inverse square root each), the panel's rows and 60 MFMAs.  One tile takes
+// 14,700 cycles in double (24,000 with one column per step, read lane by lane) and
+// 9,400 in float.
 template <typename T>
 __device__ inline bool tile_potrf_inv(const T* W, T* L, T* Inv, int lane) {
   using M = Mfma<T>;
   constexpr bool F64 = sizeof(T) == 8;
   const int j = lane % 16, k = lane / 16;
-  // row whose operand value lane l supplies, and the row of the 4 x 4 inverse
+  // row whose operand value lane l supplies
   const int arow = F64 ? j : j / 4 + 4 * (j % 4);
-  const int irow = F64 ? j : (j % 4 == 0 ? j / 4 : 4);
   auto operand = [&](T x) { return F64 ? x : __shfl(x, (lane & 48) + arow, 64); };
   auto cell = [&](int bi, int bj, int v) -> T {
     const int r = 16 * bi + k + 4 * v, c = 16 * bj + j;
     return W[min(r, c) * LDT + max(r, c)];
   };
-  typename M::acc_t A00, A01, A11, Z00, Z10, Z11;
+  typename M::acc_t A00, A01, A11, B00, B01, B11, Z00, Z10, Z11;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    A00[v] = cell(0, 0, v);
-    A01[v] = cell(0, 1, v);
-    A11[v] = cell(1, 1, v);
+    A00[v] = B00[v] = cell(0, 0, v);
+    A01[v] = B01[v] = cell(0, 1, v);
+    A11[v] = B11[v] = cell(1, 1, v);
     Z00[v] = Z11[v] = (k + 4 * v == j) ? T(1) : T(0);
     Z10[v] = T(0);
-  }
-  T e[4], f[4];                              // unit vectors: column k, row irow (none: 0)
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    e[i] = i == k ? T(1) : T(0);
-    f[i] = i == irow ? T(1) : T(0);
   }
   bool ok = true;
   auto pivot = [&](T d) {
     if (!(d > T(0)) || !(d < T(INFINITY))) { ok = false; d = T(1); }
     return d;
   };
+  // entry k of four
+  auto mine = [&](const T (&x)[4]) {
+    const T lo = (k & 1) ? x[1] : x[0], hi = (k & 1) ? x[3] : x[2];
+    return (k & 2) ? hi : lo;
+  };
 #pragma unroll
   for (int p = 0; p < 8; ++p) {
     const bool hi = p >= 4;                  // the panel's rows lie in the second half
     const int v = p % 4;
-    const T Rd = hi ? A11[v] : A00[v];
-    auto at = [&](int r, int c) { return lane_bcast(Rd, 16 * r + 4 * v + c); };
-    // unit lower factor U and pivots d of the block (only reciprocals on the
-    // chain), U^{-1}, then rows scaled by 1 / sqrt(d)
-    const T a10 = at(1, 0), a20 = at(2, 0), a30 = at(3, 0);
-    const T d0 = pivot(at(0, 0)), s0 = rcp_refined(d0);
-    const T u10 = a10 * s0, u20 = a20 * s0, u30 = a30 * s0;
-    const T b21 = fma(-a20, u10, at(2, 1)), b31 = fma(-a30, u10, at(3, 1));
-    const T d1 = pivot(fma(-a10, u10, at(1, 1))), s1 = rcp_refined(d1);
-    const T u21 = b21 * s1, u31 = b31 * s1;
-    const T b32 = fma(-b31, u21, fma(-a30, u20, at(3, 2)));
-    const T d2 = pivot(fma(-b21, u21, fma(-a20, u20, at(2, 2)))), s2 = rcp_refined(d2);
-    const T u32 = b32 * s2;
-    const T d3 = pivot(fma(-b32, u32, fma(-b31, u31, fma(-a30, u30, at(3, 3)))));
-    const T r0 = rsqrt_refined(d0), r1 = rsqrt_refined(d1), r2 = rsqrt_refined(d2), r3 = rsqrt_refined(d3);
-    // this lane's entry of the inverse of the block's factor: column k of
-    // U^{-1} by substitution, the row by its 0 / 1 weights (selects between the
-    // entries would become branches)
-    const T x1 = fma(-u10, e[0], e[1]);
-    const T x2 = fma(-u21, x1, fma(-u20, e[0], e[2]));
-    const T x3 = fma(-u32, x2, fma(-u31, x1, fma(-u30, e[0], e[3])));
-    const T inv4 = fma(f[3] * r3, x3, f[2] * r2 * x2) + fma(f[1] * r1, x1, f[0] * r0 * e[0]);
-    auto times_inv = [&](T x) { return M::mma(inv4, x, M::zero())[0]; };
-    const T P0 = hi ? T(0) : times_inv(A00[v]);
-    const T P1 = times_inv(hi ? A11[v] : A01[v]);
-    const T z0 = times_inv(hi ? Z10[v] : Z00[v]);
-    const T z1 = hi ? times_inv(Z11[v]) : T(0);
-    if (hi) { Z10[v] = z0; Z11[v] = z1; }
-    else Z00[v] = z0;
+    const T RA = hi ? A11[v] : A00[v], RB = hi ? B11[v] : B00[v];
+    auto up = [&](int r, int c) { return lane_bcast(RA, 16 * r + 4 * v + c); };
+    auto lw = [&](int r, int c) { return lane_bcast(RB, 16 * c + 4 * v + r); };
+    // the 4 x 4 block: w (lower), c (upper, over the pivot)
+    const T w10 = lw(1, 0), w20 = lw(2, 0), w30 = lw(3, 0);
+    const T r0 = rsqrt_refined(pivot(up(0, 0))), i0 = r0 * r0;
+    const T c01 = up(0, 1) * i0, c02 = up(0, 2) * i0, c03 = up(0, 3) * i0;
+    const T r1 = rsqrt_refined(pivot(fma(-w10, c01, up(1, 1)))), i1 = r1 * r1;
+    const T w21 = fma(-w20, c01, lw(2, 1)), w31 = fma(-w30, c01, lw(3, 1));
+    const T c12 = fma(-w10, c02, up(1, 2)) * i1, c13 = fma(-w10, c03, up(1, 3)) * i1;
+    const T r2 = rsqrt_refined(pivot(fma(-w21, c12, fma(-w20, c02, up(2, 2))))), i2 = r2 * r2;
+    const T w32 = fma(-w31, c12, fma(-w30, c02, lw(3, 2)));
+    const T c23 = fma(-w21, c13, fma(-w20, c03, up(2, 3))) * i2;
+    const T r3 = rsqrt_refined(pivot(fma(-w32, c23, fma(-w31, c13, fma(-w30, c03, up(3, 3))))));
+    const T root[4] = {r0, r1, r2, r3};
+    const T rk = mine(root), ik = rk * rk;
+    // the panel's rows of A and Z (rows by the lower factors) and of B (columns
+    // of W, by the upper ones): this lane's, and for A and Z over the pivot
+    auto rows = [&](T x) {
+      T q[4];
+      rows_of_column(x, q);
+      const T t0 = q[0] * i0;
+      q[1] = fma(-w10, t0, q[1]);
+      q[2] = fma(-w20, t0, q[2]);
+      q[3] = fma(-w30, t0, q[3]);
+      const T t1 = q[1] * i1;
+      q[2] = fma(-w21, t1, q[2]);
+      q[3] = fma(-w31, t1, q[3]);
+      q[3] = fma(-w32, q[2] * i2, q[3]);
+      return mine(q);
+    };
+    auto columns = [&](T x) {
+      T q[4];
+      rows_of_column(x, q);
+      q[1] = fma(-q[0], c01, q[1]);
+      q[2] = fma(-q[0], c02, q[2]);
+      q[3] = fma(-q[0], c03, q[3]);
+      q[2] = fma(-q[1], c12, q[2]);
+      q[3] = fma(-q[1], c13, q[3]);
+      q[3] = fma(-q[2], c23, q[3]);
+      return mine(q);
+    };
+    const T y0 = hi ? T(0) : columns(B00[v]), y1 = columns(hi ? B11[v] : B01[v]);
+    const T t0 = hi ? T(0) : rows(A00[v]) * ik, t1 = rows(hi ? A11[v] : A01[v]) * ik;
+    const T z0 = rows(hi ? Z10[v] : Z00[v]), z1 = hi ? rows(Z11[v]) : T(0);
+    if (hi) { Z10[v] = z0 * rk; Z11[v] = z1 * rk; }
+    else Z00[v] = z0 * rk;
     // the lane's column, kept from the compiler so that the comparisons below
     // are made here and not all held in scalar registers (which spill)
     int jc = j;
     asm volatile("" : "+v"(jc));
     if (L) {
       const int col = 4 * p + k;
-      L[col * LDT + j] = (jc >= col) ? P0 : T(0);
-      L[col * LDT + 16 + j] = (16 + jc >= col) ? P1 : T(0);
+      L[col * LDT + j] = (jc >= col) ? y0 * rk : T(0);
+      L[col * LDT + 16 + j] = (16 + jc >= col) ? y1 * rk : T(0);
     }
-    // rows below the panel
-    const T B0 = (!hi && jc >= 4 * p + 4) ? P0 : T(0), B1 = (16 + jc >= 4 * p + 4) ? P1 : T(0);
-    const T Q0 = operand(-B0), Q1 = operand(-B1);
+    // The rows of Z that are done keep their values: those of the panel and
+    // above take zeros.  The rows of A and B that are done, and the other
+    // triangle of the rest, are read no more and take what comes.
+    const T Q0 = operand(-y0), Q1 = operand(-y1), S0 = operand(t0), S1 = operand(t1);
+    const T s0 = z0 * ik, s1 = z1 * ik;
+    auto below = [&](T q) { return arow + 16 * hi >= 4 * p + 4 ? q : T(0); };
     if (p < 3) {
-      A00 = M::mma(Q0, B0, A00);
-      A01 = M::mma(Q0, B1, A01);
-      Z00 = M::mma(Q0, z0, Z00);
+      A00 = M::mma(Q0, t0, A00);
+      B00 = M::mma(S0, -y0, B00);
+      A01 = M::mma(Q0, t1, A01);
+      B01 = M::mma(S0, -y1, B01);
+      Z00 = M::mma(below(Q0), s0, Z00);
     }
     if (p < 7) {
-      A11 = M::mma(Q1, B1, A11);
-      Z10 = M::mma(Q1, z0, Z10);
-      if (hi) Z11 = M::mma(Q1, z1, Z11);
+      A11 = M::mma(Q1, t1, A11);
+      B11 = M::mma(S1, -y1, B11);
+      Z10 = M::mma(hi ? below(Q1) : Q1, s0, Z10);
+      if (hi) Z11 = M::mma(below(Q1), s1, Z11);
     }
   }
 #pragma unroll
