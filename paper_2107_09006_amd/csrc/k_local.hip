@@ -39,9 +39,9 @@ __global__ void k_entry_owner(int64_t nnz, const int32_t* __restrict__ colind, c
 // meets, one atomicMin per column into F8 (one entry per eight rows).  With
 // fac null that envelope is all it finds.
 // With scl given (S = diag(C_ii)^{-1/2} per local position, which is
-// 1 / ||A(:, c)||: C_ii holds whole columns of A), the result is S C_ii S and
-// S Ct_GG S, with unit diagonal entries on the padding positions (the
-// equilibration in one pass).
+// 1 / ||A(:, c)||: C_ii holds whole columns of A), every product is scaled as it
+// is added, so the result is S C_ii S and S Ct_GG S directly, with unit diagonal
+// entries on the padding positions (the equilibration in one pass).
 //
 // What bounds it: the look-ups of the entries' positions and the factor array
 // written once.  One thread per column, adding every product to its place in
@@ -158,6 +158,7 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
         const int k0 = __shfl(ext0, t * CPW + u, 64), k1 = __shfl(ext1, t * CPW + u, 64);
         const bool real = k0 < k1;                       // every column of Omega_i has an entry
         double* mine = acc + u * (NTL * TS);
+        const double sa = sl ? sl[pos] : 1.0;
         for (int pass = 0; pass < npass; ++pass) {
           const int qa = iv && real ? iv[pos] : 0;
           int fmin = qa;
@@ -180,8 +181,10 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
               if (iv) fmin = min(fmin, iv[pc]);
               if (!A || pc < pos) continue;
               const int sI = slot(pc / TS);
-              if (sI >= 0) __builtin_amdgcn_ds_atomic_fadd_f64(
-                  (__attribute__((address_space(3))) double*)(mine + sI * TS + pc % TS), v * va);
+              if (sI < 0) continue;
+              const int at = sI * TS + pc % TS;
+              const double x = sl ? v * va * (sa * sScl[at]) : v * va;
+              __builtin_amdgcn_ds_atomic_fadd_f64((__attribute__((address_space(3))) double*)(mine + at), x);
             }
           }
           if (iv && pass == 0 && I0 == J) {
@@ -194,17 +197,15 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
           for (int w = 0; w < CPW; ++w) {
             const int pw = column(t, w);
             const bool rw = pw < d.nI || (pw >= d.nIp && pw < d.nIp + d.nG);
-            const double sa = sl ? sl[pw] : 1.0;
             double* from = acc + w * (NTL * TS);
             for (int s = lane / (TS / 2); s < cnt; s += 128 / TS) {
               const int rr = lane % (TS / 2) * 2, row = sList[s] * TS + rr;
               double2* at = reinterpret_cast<double2*>(from + s * TS + rr);
               double2 v = *at;
               *at = double2{0.0, 0.0};
-              if (sl) {
-                const double2 sr = *reinterpret_cast<const double2*>(sScl + s * TS + rr);
-                v.x = !rw && row == pw ? 1.0 : v.x * (sa * sr.x);
-                v.y = !rw && row + 1 == pw ? 1.0 : v.y * (sa * sr.y);
+              if (sl && !rw) {
+                v.x = row == pw ? 1.0 : 0.0;
+                v.y = row + 1 == pw ? 1.0 : 0.0;
               }
               if (pass == 0) *reinterpret_cast<double2*>(A + sBase[s] + (pw - J * TS) * TS + rr) = v;
               else if (row >= d.nIp)

@@ -44,3 +44,19 @@ def test_local_matrices(n, parts, half, k):
         kappa = max(kappa, ki)
     s.close()
     assert np.linalg.norm(z - ref) <= 10 * 2.0 ** -53 * kappa * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("kind", ["grid", "irregular"])
+def test_setups_agree_to_the_bit(kind):
+    """The products of a column are added in a fixed order: two handles of the
+    same matrix apply the same preconditioner, bit for bit."""
+    import torch
+    import paper_2107_09006_amd as L
+    p = W.grid_gradient(60, 3, seed=2) if kind == "grid" else W.irregular_clustered(9000, 18000, 6, seed=2)
+    r = torch.as_tensor(np.random.default_rng(5).standard_normal(p.n)).cuda()
+    z = []
+    for _ in range(2):
+        s = L.solver_from_problem(p)
+        z.append(s.apply_preconditioner(r).cpu().numpy())
+        s.close()
+    assert np.array_equal(z[0], z[1])
