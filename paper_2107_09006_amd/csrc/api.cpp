@@ -14,6 +14,7 @@
 
 #include "ctx.hpp"
 #include "krylov.hpp"
+#include "plan_dev.hpp"
 
 namespace lsq2l {
 
@@ -171,10 +172,9 @@ void host_block_give(void* p, size_t bytes) {
 
 using namespace lsq2l;
 
-lsq2l_status lsq2l_ctx::raw_alloc(void** v, size_t bytes) {
-  int dev = 0;
-  LSQ2L_HIP_TRY(hipGetDevice(&dev));
-  size_t got = 0;
+lsq2l_status lsq2l::device_block(void** v, size_t bytes, size_t* got, int* dev) {
+  *v = nullptr;
+  LSQ2L_HIP_TRY(hipGetDevice(dev));
   // eight sizes per power of two: problems that are alike ask for the same
   // blocks, and a setup on new inputs finds what an earlier one left (with
   // the sizes as asked, irregular matrices of 1e6 columns took 182 ms instead
@@ -182,10 +182,7 @@ lsq2l_status lsq2l_ctx::raw_alloc(void** v, size_t bytes) {
   size_t step = (size_t)1 << 20;
   while (step * 16 <= bytes) step *= 2;
   bytes = (bytes + step - 1) / step * step;
-  if ((*v = cache_take(bytes, dev, &got)) != nullptr) {
-    dev_allocs.push_back({*v, got, dev});
-    return LSQ2L_OK;
-  }
+  if ((*v = cache_take(bytes, *dev, got)) != nullptr) return LSQ2L_OK;
   hipError_t e = hipMalloc(v, bytes);
   if (e != hipSuccess) {
     cache_release();
@@ -195,7 +192,15 @@ lsq2l_status lsq2l_ctx::raw_alloc(void** v, size_t bytes) {
     set_error("device allocation of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(e));
     return LSQ2L_ENOMEM;
   }
-  dev_allocs.push_back({*v, bytes, dev});
+  *got = bytes;
+  return LSQ2L_OK;
+}
+
+lsq2l_status lsq2l_ctx::raw_alloc(void** v, size_t bytes) {
+  DevBlock b{};
+  TRY(device_block(&b.p, bytes, &b.bytes, &b.dev));
+  dev_allocs.push_back(b);
+  *v = b.p;
   return LSQ2L_OK;
 }
 
@@ -623,6 +628,41 @@ struct MapsJob {
   void start(int32_t n, HostPlan* H) {
     th = std::thread([this, n, H]() { ok = plan_maps(n, *H, err); });
   }
+  // of a plan made on the device: its index sets for the handle's queries and
+  // the pairs, copied on a stream of the thread's own beside the setup's work
+  // (the device has finished both)
+  void start(HostPlan* H, const DevPlan& P, const DevicePlan& D) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const int32_t *omega = P.omega, *xi = P.xi;
+    th = std::thread([this, H, omega, xi, D, dev]() {
+      const SubDesc& last = H->subs.back();
+      hipStream_t s = nullptr;
+      HostVec<int32_t> rec;
+      ok = H->omega.resize((size_t)(last.omega_off + last.nI + last.nG)) &&
+           H->xi.resize((size_t)(last.xi_off + last.nXi)) && rec.resize((size_t)(4 * D.npairs));
+      if (!ok) { err = "host allocation failed"; return; }
+      hipError_t e = hipSetDevice(dev);
+      if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+      auto copy = [&](HostVec<int32_t>& dst, const void* src) {
+        if (e == hipSuccess && dst.size())
+          e = hipMemcpyAsync(dst.data(), src, dst.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+      };
+      copy(rec, D.pairs);
+      hipError_t w = s ? hipStreamSynchronize(s) : hipSuccess;
+      if (e == hipSuccess) e = w;
+      copy(H->omega, omega);
+      copy(H->xi, xi);
+      if (e == hipSuccess) plan_pairs(rec.data(), rec.size(), *H);
+      w = s ? hipStreamSynchronize(s) : hipSuccess;
+      if (e == hipSuccess) e = w;
+      if (s) (void)hipStreamDestroy(s);
+      if (e != hipSuccess) {
+        ok = false;
+        err = std::string("reading the plan: ") + hipGetErrorString(e);
+      }
+    });
+  }
   bool join() {
     if (th.joinable()) th.join();
     return ok;
@@ -800,11 +840,73 @@ void pack_solve_stream(lsq2l_ctx* c, hipStream_t st) {
     launch_stream_pack<double>(st, c->nsub, c->P, c->fac, c->dinv, c->ss);
 }
 
+// Device-to-host copy of the concatenated column indices in chunks, each
+// closed by an event.  head closes everything queued before the chunks.  The
+// destructor waits for the last chunk, so the pinned buffer is never handed
+// back while a copy into it is in flight (also on early error returns).
+struct PatternChunks {
+  static constexpr int NCH = 8;
+  hipEvent_t head = nullptr;
+  hipEvent_t ev[NCH] = {};
+  int64_t bound[NCH + 1] = {};
+  int nch = 0;
+  lsq2l_status start(hipStream_t st, int32_t* host, const int32_t* dev, int64_t nnz) {
+    LSQ2L_HIP_TRY(hipEventCreateWithFlags(&head, hipEventDisableTiming));
+    LSQ2L_HIP_TRY(hipEventRecord(head, st));
+    const int want = nnz >= ((int64_t)1 << 20) ? NCH : (nnz > 0 ? 1 : 0);
+    for (int q = 0; q < want; ++q) {
+      const int64_t a = nnz * q / want, b = nnz * (q + 1) / want;
+      LSQ2L_HIP_TRY(hipEventCreateWithFlags(&ev[q], hipEventDisableTiming));
+      nch = q + 1;
+      bound[q] = a;
+      bound[q + 1] = b;
+      if (b > a)
+        LSQ2L_HIP_TRY(hipMemcpyAsync(host + a, dev + a, (b - a) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+      LSQ2L_HIP_TRY(hipEventRecord(ev[q], st));
+    }
+    return LSQ2L_OK;
+  }
+  // returns once entries [0, upto) are in place
+  void wait(int64_t upto) const {
+    for (int q = nch - 1; q >= 0; --q)
+      if (bound[q] < upto) {              // chunks complete in order: the last one needed suffices
+        (void)hipEventSynchronize(ev[q]);
+        return;
+      }
+  }
+  ~PatternChunks() {
+    if (nch > 0) (void)hipEventSynchronize(ev[nch - 1]);
+    for (int q = 0; q < nch; ++q) (void)hipEventDestroy(ev[q]);
+    if (head) (void)hipEventDestroy(head);
+  }
+};
+
+// A's pattern on the host.  The column indices come back in chunks, each
+// closed by an event, so that the planner starts on the rows that have arrived
+// while the rest is in flight; start() returns once the row pointers and all
+// that was queued before are in place.
+struct HostPattern {
+  PinnedArray<int32_t> rp, ci;
+  PatternChunks chunks;             // waited for before the arrays go
+  bool started = false;
+  lsq2l_status start(lsq2l_ctx* c) {
+    if (started) return LSQ2L_OK;
+    const int64_t m = c->M.m;
+    TRY(rp.alloc(m + 1));
+    TRY(ci.alloc(c->M.nnz));
+    LSQ2L_HIP_TRY(hipMemcpyAsync(rp.p, c->M.rowptr, (m + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
+    started = true;
+    TRY(chunks.start(c->st, ci.p, c->M.colind, c->M.nnz));
+    const hipError_t e = hipEventSynchronize(chunks.head);
+    if (e != hipSuccess) { set_error(std::string("reading A: ") + hipGetErrorString(e)); return LSQ2L_EHIP; }
+    return LSQ2L_OK;
+  }
+};
+
 // Everything after the matrix is resident in the handle (c->M rowptr/colind/vals).
-lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
-                        const HostVec<int32_t>& part, int32_t nparts,
-                        const std::vector<int32_t>& seg_of_part,
-                        const std::function<void(int64_t)>& wait_nnz) {
+// pat holds A's pattern where the host is to plan, else it is read if need be.
+lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& part, int32_t nparts,
+                        const std::vector<int32_t>& seg_of_part) {
   const hipStream_t st = c->st;
   const int32_t m = c->M.m, n = c->M.n;
   const int64_t nnz = c->M.nnz;
@@ -827,30 +929,46 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
   launch_row_blocks(st, n, c->M.trowptr, nnz, c->M.tblk);
   c->M.spmv_group = pick_group(m ? (double)nnz / m : 1.0);
   c->M.spmvt_group = pick_group(n ? (double)nnz / n : 1.0);
-  std::string err;
-  if (!plan_build(m, n, rp, ci, part.data(), nparts, seg_of_part, c->H, err, wait_nnz)) {
-    set_error(err);
-    return LSQ2L_EINVAL;
-  }
-  // Row order of the copy used for C p = A^T (A p), found on a host thread
-  // while the device assembles, factors and selects (see row_order); started
-  // once the planner's threads are done, so that it takes none of their cores.
-  RowOrder ro;
-  JoiningThread ro_thread{std::thread([&ro, m, n, rp, ci, nnz, &wait_nnz]() {
-    if (wait_nnz) wait_nnz(nnz);
-    row_order(m, n, rp, ci, ro);
-  })};
   HostPlan& H = c->H;
   c->nsub = nparts;
-  MapsJob maps;
-  maps.start(n, &H);
-  TRY(c->upload(&c->P.subs, H.subs));
-  TRY(c->upload(&c->P.omega, H.omega));
-  TRY(c->upload(&c->P.xi, H.xi));
   TRY(c->upload(&c->P.part, part));
-  TRY(c->upload(&c->P.locown, H.locown));
-  TRY(c->upload(&c->P.tileF, H.tileF));
-  TRY(c->upload(&c->P.tileOff, H.tileOff));
+  Scratch work(st);                // given back with the setup
+  int2* owner = nullptr;
+  TRY(work.alloc(&owner, nnz));
+  DevicePlan D;
+  if (!pat.started) {
+    const lsq2l_status s = plan_build_device(c, nparts, seg_of_part, owner, work, D);
+    if (s == LSQ2L_EINVAL || s == LSQ2L_EHIP) return s;
+  }
+  RowOrder ro;
+  JoiningThread ro_thread;
+  MapsJob maps;
+  if (D.done) {
+    maps.start(&H, c->P, D);
+  } else {
+    TRY(pat.start(c));
+    std::string err;
+    if (!plan_build(m, n, pat.rp.p, pat.ci.p, part.data(), nparts, seg_of_part, H, err,
+                    [&pat](int64_t e) { pat.chunks.wait(e); })) {
+      set_error(err);
+      return LSQ2L_EINVAL;
+    }
+    // Row order of the copy used for C p = A^T (A p), found on a host thread
+    // while the device assembles, factors and selects (see row_order); started
+    // once the planner's threads are done, so that it takes none of their cores.
+    ro_thread.t = std::thread([&ro, &pat, m, n, nnz]() {
+      pat.chunks.wait(nnz);
+      row_order(m, n, pat.rp.p, pat.ci.p, ro);
+    });
+    maps.start(n, &H);
+    TRY(c->upload(&c->P.subs, H.subs));
+    TRY(c->upload(&c->P.omega, H.omega));
+    TRY(c->upload(&c->P.xi, H.xi));
+    TRY(c->upload(&c->P.locown, H.locown));
+    TRY(c->upload(&c->P.tileF, H.tileF));
+    TRY(c->upload(&c->P.tileOff, H.tileOff));
+    launch_entry_owner(st, c->P, c->M, owner);
+  }
   c->P.min_nG = INT32_MAX;
   for (const SubDesc& d : H.subs) {
     c->P.max_np = std::max(c->P.max_np, (int)d.np);
@@ -896,9 +1014,6 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
     LSQ2L_HIP_TRY(hipMemsetAsync(c->fac, 0, H.total_fac * sizeof(double), st));
   if (H.total_g) LSQ2L_HIP_TRY(hipMemsetAsync(c->ctg, 0, H.total_g * sizeof(double), st));
   TRY(solve_layout_begin(c));
-  int2* owner = nullptr;
-  TRY(c->dalloc(&owner, nnz));
-  launch_entry_owner(st, c->P, c->M, owner);
   const bool qr = c->opt.local_factor == LSQ2L_FACTOR_QR;
   if (qr) {
     // QR local factors (Remarks 3.1, 3.2): no C_ii is formed.  The pattern
@@ -1296,11 +1411,13 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
   }
   // --- overlap maps (owners of every column, for the scatter)
   if (!maps.join()) { set_error(maps.err); return LSQ2L_EINVAL; }
-  TRY(c->upload(&c->P.own_ptr, H.own_ptr));
-  TRY(c->upload(&c->P.own_pos, H.own_pos));
+  if (!D.done) {
+    TRY(c->upload(&c->P.own_ptr, H.own_ptr));
+    TRY(c->upload(&c->P.own_pos, H.own_pos));
+    ro_thread.t.join();
+  }
   // --- row-permuted iteration copy of A
-  ro_thread.t.join();
-  c->row_perm = ro.use;
+  c->row_perm = D.done ? row_order_use(m, D.far_descents) : ro.use;
   if (c->row_perm) {
     DevMatrix& Mi = c->Mi;
     Mi.m = m;
@@ -1315,8 +1432,13 @@ lsq2l_status setup_core(lsq2l_ctx* c, const int32_t* rp, const int32_t* ci,
     TRY(c->dalloc(&Mi.trow, nnz));
     TRY(c->dalloc(&Mi.tperm, nnz));
     TRY(c->dalloc(&Mi.tvals, nnz));
-    TRY(c->upload(&dperm, ro.perm));
-    TRY(c->upload(&Mi.rowptr, ro.prp));
+    if (D.done) {
+      TRY(c->dalloc(&Mi.rowptr, (int64_t)m + 1));
+      TRY(row_order_device(c, work, &dperm, Mi.rowptr));
+    } else {
+      TRY(c->upload(&dperm, ro.perm));
+      TRY(c->upload(&Mi.rowptr, ro.prp));
+    }
     launch_permute_rows(st, m, dperm, c->M.rowptr, c->M.colind, c->M.vals, Mi.rowptr, Mi.colind, Mi.vals);
     LSQ2L_HIP_TRY(launch_transpose(st, m, n, nnz, Mi.rowptr, Mi.colind, Mi.vals, Mi.trowptr, Mi.trow,
                                    Mi.tvals, Mi.tperm, temp, tb));
@@ -1445,47 +1567,6 @@ bool is_device_ptr(const void* p) {
   return at.type == hipMemoryTypeDevice;
 }
 
-// Device-to-host copy of the concatenated column indices in chunks, each
-// closed by an event.  head closes everything queued before the chunks.  The
-// destructor waits for the last chunk, so the pinned buffer is never handed
-// back while a copy into it is in flight (also on early error returns).
-struct PatternChunks {
-  static constexpr int NCH = 8;
-  hipEvent_t head = nullptr;
-  hipEvent_t ev[NCH] = {};
-  int64_t bound[NCH + 1] = {};
-  int nch = 0;
-  lsq2l_status start(hipStream_t st, int32_t* host, const int32_t* dev, int64_t nnz) {
-    LSQ2L_HIP_TRY(hipEventCreateWithFlags(&head, hipEventDisableTiming));
-    LSQ2L_HIP_TRY(hipEventRecord(head, st));
-    const int want = nnz >= ((int64_t)1 << 20) ? NCH : (nnz > 0 ? 1 : 0);
-    for (int q = 0; q < want; ++q) {
-      const int64_t a = nnz * q / want, b = nnz * (q + 1) / want;
-      LSQ2L_HIP_TRY(hipEventCreateWithFlags(&ev[q], hipEventDisableTiming));
-      nch = q + 1;
-      bound[q] = a;
-      bound[q + 1] = b;
-      if (b > a)
-        LSQ2L_HIP_TRY(hipMemcpyAsync(host + a, dev + a, (b - a) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-      LSQ2L_HIP_TRY(hipEventRecord(ev[q], st));
-    }
-    return LSQ2L_OK;
-  }
-  // returns once entries [0, upto) are in place
-  void wait(int64_t upto) const {
-    for (int q = nch - 1; q >= 0; --q)
-      if (bound[q] < upto) {              // chunks complete in order: the last one needed suffices
-        (void)hipEventSynchronize(ev[q]);
-        return;
-      }
-  }
-  ~PatternChunks() {
-    if (nch > 0) (void)hipEventSynchronize(ev[nch - 1]);
-    for (int q = 0; q < nch; ++q) (void)hipEventDestroy(ev[q]);
-    if (head) (void)hipEventDestroy(head);
-  }
-};
-
 // Setup of one or several instances: their CSR arrays are concatenated and
 // checked on the device in three launches (launch_concat), and the
 // concatenated pattern is read back once into pinned memory for the planner.
@@ -1533,12 +1614,8 @@ lsq2l_status setup_instances(lsq2l_ctx* c, int count, const lsq2l_problem* probs
   TRY(c->upload(&d_desc, desc));
   TRY(c->dalloc(&d_bad, CSR_KINDS));
   launch_concat(st, count, d_desc, M, NNZ, c->M.rowptr, c->M.colind, c->M.vals, d_bad);
-  PinnedArray<int32_t> rp, ci;
-  TRY(rp.alloc(M + 1));
-  TRY(ci.alloc(NNZ));
   unsigned long long hbad[CSR_KINDS];
   LSQ2L_HIP_TRY(hipMemcpyAsync(hbad, d_bad, sizeof(hbad), hipMemcpyDeviceToHost, st));
-  LSQ2L_HIP_TRY(hipMemcpyAsync(rp.p, c->M.rowptr, (M + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   // partitions: host arrays are read in place, device arrays copied back
   HostVec<int32_t> pt;
   std::vector<int32_t> seg_of_part(NP);
@@ -1549,12 +1626,12 @@ lsq2l_status setup_instances(lsq2l_ctx* c, int count, const lsq2l_problem* probs
       TRY(pdev[k].alloc(probs[k].n));
       LSQ2L_HIP_TRY(hipMemcpyAsync(pdev[k].p, probs[k].part, probs[k].n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     }
-  // the column indices come back in chunks, each closed by an event, so that
-  // the planner starts on the rows that have arrived while the rest is in
-  // flight (the checks, row pointers and parts are waited for here)
-  PatternChunks chunks;
-  TRY(chunks.start(st, ci.p, c->M.colind, NNZ));
-  const hipError_t e = hipEventSynchronize(chunks.head);
+  // where the host plans, the pattern comes back too (the checks, row
+  // pointers and parts are waited for here)
+  HostPattern pat;
+  hipError_t e = hipSuccess;
+  if (NNZ < DEVICE_PLAN_NNZ) TRY(pat.start(c));
+  else e = hipStreamSynchronize(st);
   if (e != hipSuccess) { set_error(std::string("reading A: ") + hipGetErrorString(e)); return LSQ2L_EHIP; }
   // the first failure in the order of the checks: row extents, then columns
   // (reported only when the extents hold)
@@ -1603,8 +1680,7 @@ lsq2l_status setup_instances(lsq2l_ctx* c, int count, const lsq2l_problem* probs
   for (int k = 0; k < count; ++k)
     for (int32_t q = 0; q < probs[k].nparts; ++q) seg_of_part[p0[k] + q] = k;
   c->info.t_prepare_ms = ms_since(t_prep);
-  return setup_core(c, rp.p, ci.p, pt, (int32_t)NP, seg_of_part,
-                    [&chunks](int64_t e) { chunks.wait(e); });
+  return setup_core(c, pat, pt, (int32_t)NP, seg_of_part);
 }
 
 lsq2l_ctx* new_handle(double tau, const lsq2l_options* opt, void* hip_stream) {

@@ -26,6 +26,8 @@ inline double ms_since(clk::time_point t0) {
 // Device blocks of destroyed handles, kept for later handles on the same
 // device (api.cpp).
 void* cache_take(size_t bytes, int dev, size_t* got);
+// a block of at least the given size on the current device, from the cache or new
+lsq2l_status device_block(void** p, size_t bytes, size_t* got, int* dev);
 void cache_give(void* p, size_t bytes, int dev);
 void cache_release();
 

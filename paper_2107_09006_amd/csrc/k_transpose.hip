@@ -128,6 +128,11 @@ static void exclusive_scan(hipStream_t st, int64_t n, int32_t* v, int32_t* work)
   k_scan_apply<<<nt, SCAN_THREADS, 0, st>>>(n, v, work);
 }
 
+int64_t scan_work_len(int64_t n) { return scan_tiles(n) + 1; }
+void launch_exclusive_scan(hipStream_t st, int64_t n, int32_t* v, int32_t* work) {
+  exclusive_scan(st, n, v, work);
+}
+
 // ---------------------------------------------------------------------------
 // radix sort passes
 // ---------------------------------------------------------------------------

@@ -213,6 +213,45 @@ void launch_multi_gemv(hipStream_t st, int S, const int64_t* seg_ptr, int64_t n,
 void launch_normalize_seg(hipStream_t st, int64_t n, int S, const int64_t* seg_ptr,
                           const double* nrm2, const int32_t* done, const double* a, double* out);
 
+// --- device planner ----------------------------------------------------------
+// in-place exclusive scan of v[0 .. n); work: scan_work_len(n) int32
+int64_t scan_work_len(int64_t n);
+void launch_exclusive_scan(hipStream_t st, int64_t n, int32_t* v, int32_t* work);
+// see k_plan.hip; with out null the counting pass
+void launch_iota(hipStream_t st, int64_t n, int32_t* out);
+void launch_locown(hipStream_t st, int32_t n, const int32_t* pcols, const int32_t* part, const int32_t* pptr,
+                   int32_t* locown);
+void launch_row_runs(hipStream_t st, int32_t m, const int32_t* rowptr, const int2* owner, int32_t* ptr,
+                     int32_t* out);
+void launch_seg_first(hipStream_t st, int32_t nseg, int64_t len, const int32_t* ptr, const int32_t* key,
+                      int32_t* first);
+void launch_seg_pack(hipStream_t st, int32_t nseg, int64_t len, const int32_t* ptr, const int32_t* key,
+                     const int32_t* at, int32_t* out, int32_t* optr);
+void launch_plan_stat(hipStream_t st, const DevMatrix& M, int32_t jump, unsigned long long* stat);
+void launch_plan_size(hipStream_t st, int32_t m, const int32_t* rowptr, const int32_t* qptr,
+                      unsigned long long* size);
+void launch_col_parts(hipStream_t st, int32_t n, const int32_t* trowptr, const int32_t* trow,
+                      const int32_t* qptr, const int32_t* qpart, const int32_t* part, int32_t* ptr,
+                      int32_t* out);
+void launch_plan_omega(hipStream_t st, int32_t nsub, const SubDesc* subs, const int32_t* pptr,
+                       const int32_t* pcols, const int32_t* goff, const int32_t* gamma, int32_t* omega,
+                       int32_t* F);
+void launch_plan_envelope(hipStream_t st, const int32_t* qptr, const int32_t* qpart, const DevMatrix& M,
+                          const int2* owner, const SubDesc* subs, const int32_t* goff,
+                          const int32_t* gamma, int32_t* F);
+void launch_tile_offsets(hipStream_t st, int32_t nsub, const SubDesc* subs, const int32_t* F, int64_t* off,
+                         int64_t* stored);
+void launch_own_maps(hipStream_t st, int32_t n, const int32_t* part, const int32_t* locown,
+                     const SubDesc* subs, const int32_t* goff, const int32_t* optr, const int32_t* opart,
+                     const int32_t* operm, int32_t* own_ptr, int32_t* own_pos);
+void launch_pair_count(hipStream_t st, int64_t nx, const int32_t* xi, const int32_t* qperm,
+                       const int32_t* qptr, int32_t* cnt);
+void launch_pair_fill(hipStream_t st, int64_t nx, const int32_t* qperm, const int32_t* qpart,
+                      const int32_t* xoff, const int32_t* at, int4* rec);
+void launch_row_keys(hipStream_t st, int32_t m, int32_t n, const int32_t* rowptr, const int32_t* colind,
+                     int32_t* key);
+void launch_perm_len(hipStream_t st, int32_t m, const int32_t* perm, const int32_t* rowptr, int32_t* len);
+
 // --- subdomain kernels -------------------------------------------------------
 // with inv (not null), also the envelope F8 of the global-order layouts gsub:
 // per eight rows the first position they reach (launch_solve_env_init first)

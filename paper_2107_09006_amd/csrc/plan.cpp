@@ -462,42 +462,48 @@ bool plan_maps(int32_t n, HostPlan& P, std::string& err) {
           std::sort(P.own_pos.begin() + P.own_ptr[j], P.own_pos.begin() + P.own_ptr[j + 1]);
     });
   }
-  // pairs of subdomains sharing rows: ids in order of first occurrence (row
-  // ranges in row order), then the rows of every pair grouped by id
-  std::vector<std::vector<std::pair<int32_t, int32_t>>> adj((size_t)nparts);   // (j, id)
-  std::vector<int32_t> rid;
+  std::vector<int32_t> rec;
+  for (std::vector<int32_t>& part : P.shared_rows) {
+    if (rec.empty()) rec = std::move(part);
+    else rec.insert(rec.end(), part.begin(), part.end());
+    part = std::vector<int32_t>();
+  }
+  P.shared_rows.clear();
+  plan_pairs(rec.data(), rec.size(), P);
+  return true;
+}
+
+// pairs of subdomains sharing rows: ids in order of first occurrence (records
+// in row order), then the rows of every pair grouped by id
+void plan_pairs(const int32_t* rec, size_t len, HostPlan& P) {
+  std::vector<std::vector<std::pair<int32_t, int32_t>>> adj((size_t)P.nparts);   // (j, id)
+  std::vector<int32_t> rid(len / 4);
   std::vector<int64_t> pcnt;
   P.cpair_ij.clear();
-  for (const auto& rec : P.shared_rows)
-    for (size_t e = 0; e < rec.size(); e += 4) {
-      const int32_t i = rec[e], j = rec[e + 1];
-      int32_t id = -1;
-      for (const auto& pr : adj[i])
-        if (pr.first == j) { id = pr.second; break; }
-      if (id < 0) {
-        id = (int32_t)pcnt.size();
-        adj[i].push_back({j, id});
-        P.cpair_ij.push_back(i);
-        P.cpair_ij.push_back(j);
-        pcnt.push_back(0);
-      }
-      ++pcnt[id];
-      rid.push_back(id);
+  for (size_t e = 0; e < len; e += 4) {
+    const int32_t i = rec[e], j = rec[e + 1];
+    int32_t id = -1;
+    for (const auto& pr : adj[i])
+      if (pr.first == j) { id = pr.second; break; }
+    if (id < 0) {
+      id = (int32_t)pcnt.size();
+      adj[i].push_back({j, id});
+      P.cpair_ij.push_back(i);
+      P.cpair_ij.push_back(j);
+      pcnt.push_back(0);
     }
+    ++pcnt[id];
+    rid[e / 4] = id;
+  }
   P.cpair_ptr.assign(pcnt.size() + 1, 0);
   for (size_t k = 0; k < pcnt.size(); ++k) P.cpair_ptr[k + 1] = P.cpair_ptr[k] + pcnt[k];
   P.cpair_rows.resize((size_t)(2 * P.cpair_ptr.back()));
   std::vector<int64_t> cur(P.cpair_ptr.begin(), P.cpair_ptr.end() - 1);
-  size_t x = 0;
-  for (const auto& rec : P.shared_rows)
-    for (size_t e = 0; e < rec.size(); e += 4, ++x) {
-      const int64_t at = cur[rid[x]]++;
-      P.cpair_rows[2 * at] = rec[e + 2];
-      P.cpair_rows[2 * at + 1] = rec[e + 3];
-    }
-  P.shared_rows.clear();
-  P.shared_rows.shrink_to_fit();
-  return true;
+  for (size_t e = 0; e < len; e += 4) {
+    const int64_t at = cur[rid[e / 4]]++;
+    P.cpair_rows[2 * at] = rec[e + 2];
+    P.cpair_rows[2 * at + 1] = rec[e + 3];
+  }
 }
 
 void plan_coarse(HostPlan& H, int S, int32_t m, const std::vector<int32_t>& ph, CoarsePlan& C) {
@@ -605,10 +611,9 @@ void row_order(int32_t m, int32_t n, const int32_t* rp, const int32_t* ci, RowOr
   auto key = [&](int32_t i) { return rp[i] < rp[i + 1] ? ci[rp[i]] : n; };
   // far descents: the first column drops by more than ROW_ORDER_JUMP (rows
   // that jitter around a slowly moving centre keep their x gathers local)
-  constexpr int32_t ROW_ORDER_JUMP = 256;
   int64_t desc = 0;
   for (int32_t i = 1; i < m; ++i) desc += key(i) < key(i - 1) - ROW_ORDER_JUMP;
-  ro.use = m >= 65536 && desc * 16 > m;
+  ro.use = row_order_use(m, desc);
   if (!ro.use) return;
   std::vector<int32_t> start((size_t)n + 2, 0);
   ro.perm.resize((size_t)m);

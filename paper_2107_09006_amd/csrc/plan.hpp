@@ -119,6 +119,8 @@ bool plan_build(int32_t m, int32_t n, const int32_t* rowptr, const int32_t* coli
 // from shared_rows, which it empties).  Reads the rest of P only, so it may
 // run while the device works on the built part.
 bool plan_maps(int32_t n, HostPlan& P, std::string& err);
+// the pairs alone, from len / 4 records in row order
+void plan_pairs(const int32_t* rec, size_t len, HostPlan& P);
 
 // Coarse numbering (per instance, subdomains in order, padded to 32), the
 // pairs of subdomains whose rows overlap (blocks of E), the tile envelope of
@@ -145,6 +147,8 @@ void plan_coarse(HostPlan& H, int S, int32_t m, const std::vector<int32_t>& p, C
 // rows), the rows sorted stably by their first column (counting sort):
 // perm[i] is the row of A placed at i, prp the row starts of the permuted copy.  The x gathers of A p
 // and the (A p) gathers of A^T (A p) then stay local.
+constexpr int32_t ROW_ORDER_JUMP = 256;
+inline bool row_order_use(int32_t m, int64_t far_descents) { return m >= 65536 && far_descents * 16 > m; }
 struct RowOrder {
   bool use = false;
   std::vector<int32_t> perm, prp;
