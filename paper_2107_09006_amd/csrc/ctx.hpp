@@ -101,6 +101,8 @@ struct lsq2l_ctx {
   lsq2l::DevMatrix M;
   lsq2l::DevMatrix Mi;      // row-permuted copy of A and its transpose for C p = A^T (A p)
   bool row_perm = false;    // Mi is in use
+  int32_t* mi_perm = nullptr;   // the row of A at each row of Mi
+  double* mi_y = nullptr;       // m: a vector in Mi's row order
   lsq2l::DevPlan P;
   lsq2l::DevCoarse Cc;
   lsq2l::HostPlan H;

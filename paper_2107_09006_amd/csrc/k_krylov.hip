@@ -82,11 +82,11 @@ __device__ inline V spmv_load(const V* p) {
   else return *p;
 }
 
-template <bool STREAM>
+template <bool STREAM, bool PLACED>
 __global__ void __launch_bounds__(SPMV_THREADS)
 k_spmv_stream(const int32_t* __restrict__ tab, const int32_t* __restrict__ rowptr,
               const int32_t* __restrict__ colind, const double* __restrict__ vals,
-              const double* __restrict__ x, double* __restrict__ y) {
+              const double* __restrict__ x, double* __restrict__ y, const int32_t* __restrict__ place) {
   __shared__ double prod[SPMV_CAP];
   const int tid = threadIdx.x;
   typedef int32_t i2 __attribute__((ext_vector_type(2)));
@@ -115,7 +115,7 @@ k_spmv_stream(const int32_t* __restrict__ tab, const int32_t* __restrict__ rowpt
       const int32_t a = rowptr[r] - e0, b = rowptr[r + 1] - e0;
       double s = 0.0;
       for (int32_t k = a; k < b; ++k) s += prod[k];
-      y[r] = s;
+      y[PLACED ? place[r] : r] = s;
     }
     return;
   }
@@ -126,23 +126,36 @@ k_spmv_stream(const int32_t* __restrict__ tab, const int32_t* __restrict__ rowpt
     for (int32_t e = rowptr[r] + lane; e < rowptr[r + 1]; e += 64) s += vals[e] * x[colind[e]];
 #pragma unroll
     for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);
-    if (lane == 0) y[r] = s;
+    if (lane == 0) y[PLACED ? place[r] : r] = s;
   }
 }
 
+// out[i] = in[perm[i]]; bound by the lines that the scattered reads touch
+__global__ void __launch_bounds__(256)
+k_gather(int64_t n, const int32_t* __restrict__ perm, const double* __restrict__ in, double* __restrict__ out) {
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k < n) out[k] = in[perm[k]];
+}
+
+void launch_gather(hipStream_t st, int64_t n, const int32_t* perm, const double* in, double* out) {
+  if (n == 0) return;
+  k_gather<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(n, perm, in, out);
+}
+
+// with place, row r of the product goes to y[place[r]] (row blocks only)
 // group 0: row blocks, streaming loads if the matrix arrays (12 bytes per
 // entry) exceed the last-level cache; -1 / -2: row blocks with cached /
 // streaming loads; 1 .. 64: that many lanes per row
 void launch_spmv(hipStream_t st, int32_t nrows, const int32_t* rowptr, const int32_t* colind,
                  const double* vals, const double* x, double* y, int group, int64_t nnz,
-                 const int32_t* blk) {
+                 const int32_t* blk, const int32_t* place) {
   if (nrows == 0) return;
   if (group == 0) group = 12 * nnz > SPMV_STREAM_BYTES ? SPMV_ROWS_STREAM : SPMV_ROWS_CACHED;
   if (group < 0 && blk) {
-    if (group == SPMV_ROWS_STREAM)
-      k_spmv_stream<true><<<(unsigned)spmv_blocks(nnz), SPMV_THREADS, 0, st>>>(blk, rowptr, colind, vals, x, y);
-    else
-      k_spmv_stream<false><<<(unsigned)spmv_blocks(nnz), SPMV_THREADS, 0, st>>>(blk, rowptr, colind, vals, x, y);
+    const bool str = group == SPMV_ROWS_STREAM;
+    auto* kernel = place ? (str ? k_spmv_stream<true, true> : k_spmv_stream<false, true>)
+                         : (str ? k_spmv_stream<true, false> : k_spmv_stream<false, false>);
+    kernel<<<(unsigned)spmv_blocks(nnz), SPMV_THREADS, 0, st>>>(blk, rowptr, colind, vals, x, y, place);
     return;
   }
   if (group < 0) group = 1;

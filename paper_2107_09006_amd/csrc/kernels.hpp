@@ -117,7 +117,9 @@ void launch_check_cols(hipStream_t st, int64_t nnz, const int32_t* colind, int32
 enum { SPMV_ROWS_CACHED = -1, SPMV_ROWS_STREAM = -2 };
 void launch_spmv(hipStream_t st, int32_t nrows, const int32_t* rowptr, const int32_t* colind,
                  const double* vals, const double* x, double* y, int group, int64_t nnz,
-                 const int32_t* blk);
+                 const int32_t* blk,
+                 const int32_t* place = nullptr);
+void launch_gather(hipStream_t st, int64_t n, const int32_t* perm, const double* in, double* out);
 // the LDS row blocks of a CSR matrix: spmv_blocks(nnz) blocks, described by
 // a table of spmv_table_len(nnz) int32 (first row and its start, per block)
 int64_t spmv_blocks(int64_t nnz);

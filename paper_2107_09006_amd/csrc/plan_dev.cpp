@@ -222,7 +222,7 @@ lsq2l_status plan_build_device(lsq2l_ctx* c, int32_t nparts, const std::vector<i
   return LSQ2L_OK;
 }
 
-lsq2l_status row_order_device(lsq2l_ctx* c, Scratch& tmp, int32_t** perm, int32_t* prp) {
+lsq2l_status row_order_device(lsq2l_ctx* c, Scratch& tmp, int32_t* perm, int32_t* prp) {
   const hipStream_t st = c->st;
   const DevMatrix& M = c->M;
   Sorter S{st, tmp};
@@ -230,12 +230,11 @@ lsq2l_status row_order_device(lsq2l_ctx* c, Scratch& tmp, int32_t** perm, int32_
   TRY(tmp.alloc(&iota, (int64_t)M.m + 1));
   TRY(tmp.alloc(&key, M.m));
   TRY(tmp.alloc(&kptr, (int64_t)M.n + 2));
-  TRY(tmp.alloc(perm, M.m));
   TRY(tmp.alloc(&again, M.m));
   launch_iota(st, (int64_t)M.m + 1, iota);
   launch_row_keys(st, M.m, M.n, M.rowptr, M.colind, key);
-  TRY(S.sort(M.m, M.n + 1, M.m, iota, key, kptr, *perm, again));
-  launch_perm_len(st, M.m, *perm, M.rowptr, prp);
+  TRY(S.sort(M.m, M.n + 1, M.m, iota, key, kptr, perm, again));
+  launch_perm_len(st, M.m, perm, M.rowptr, prp);
   return S.scan((int64_t)M.m + 1, prp);
 }
 

@@ -56,6 +56,6 @@ lsq2l_status plan_build_device(lsq2l_ctx* c, int32_t nparts, const std::vector<i
                                int2* owner, Scratch& keep, DevicePlan& out);
 
 // The order of row_order on the device: perm and row pointer of the copy
-lsq2l_status row_order_device(lsq2l_ctx* c, Scratch& tmp, int32_t** perm, int32_t* prp);
+lsq2l_status row_order_device(lsq2l_ctx* c, Scratch& tmp, int32_t* perm, int32_t* prp);
 
 }  // namespace lsq2l
