@@ -113,6 +113,7 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
   __shared__ int32_t sF[QR_TMAX], sO[QR_TMAX], sGen[QR_TMAX], sRows[QR_TMAX], sBuf[QR_CH];
   __shared__ uint8_t sNZ[QR_TMAX];       // tile of the list left nonzero in the block
   __shared__ int s_jmin, s_jmax, s_count, s_fail, s_q;
+  __shared__ int s_done, s_next;         // reflectors in LDS; tiles right of J taken
   __shared__ int s_scan[4];
   const SubDesc d = subs[blockIdx.x];
   const SubDesc pd = psubs[d.id];
@@ -135,7 +136,7 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
       sO[I] = (int32_t)tileOff[d.tile_base + I];
     }
   for (int I = tid; I < ntiles; I += QR_THREADS) sGen[I] = -1;
-  if (tid == 0) s_fail = 0;
+  if (tid == 0) { s_fail = 0; s_done = 0; s_next = 0; }
   double* Lf = MODE == QR_GAMMA ? out + pd.g_off : out + d.fac_off;
   double* Di = MODE == QR_GAMMA ? nullptr : dinv + d.dinv_off;
   double* Bs = strip + (int64_t)QB * pd.loc_off;
@@ -235,15 +236,15 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
     const int gen = (int)blk++;
     if (tid == 0) { s_jmin = INT_MAX; s_jmax = -1; }
     __syncthreads();
-    // ---- the rows of the block into the strip (one thread per row)
-    if (tid < nrow) {
-      const int r = sBuf[head + tid];
+    // ---- the rows of the block into the strip (eight threads per row)
+    if (tid / 8 < nrow) {
+      const int br = tid / 8, r = sBuf[head + br];
       int jmin = INT_MAX, jmax = -1;
-      for (int e = rowptr[r]; e < rowptr[r + 1]; ++e) {
+      for (int e = rowptr[r] + tid % 8; e < rowptr[r + 1]; e += 8) {
         int posP;
         const int pos = layout_pos(colind[e], &posP);
         if (pos < 0) continue;
-        Bs[(int64_t)pos * QB + tid] = vals[e] * scale[pd.loc_off + posP];
+        Bs[(int64_t)pos * QB + br] = vals[e] * scale[pd.loc_off + posP];
         const int K = pos / TS;
         sGen[K] = gen;
         jmin = min(jmin, K);
@@ -265,12 +266,15 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
       } else {
         nr = envelope_rows(sF, J, ntiles, sRows, QR_TMAX, &s_count);
       }
-      for (int a = tid; a < nr; a += QR_THREADS) sNZ[a] = 0;
       // panel: the triangle R(J, J) over B(:, J), on wave 0.  Lane (kc, h)
       // holds column kc of the tile, B rows 16 h .. 16 h + 15 and R rows
       // 16 h .. 16 h + 15; a column's two lanes are 32 apart, so its sums
       // take one lane swap and no workgroup barrier is needed.  Reflector c
-      // goes to LDS (sV, sTau) for the other columns and the trailing tiles.
+      // goes to LDS (sV, sTau) for the other columns, and s_done lets the other
+      // waves, which already hold their tiles right of J, apply it.  The chain
+      // of the 32 columns, 1,100 cycles each, bounds the kernel: 32 subdomains of
+      // 940 columns take 5.5 ms (interior factor) and 4.7 (solve factor), 6.0 and
+      // 5.5 with the tiles right of J after the panel.
       double* Rjj = rtile(J, J);
       if (wave == 0) {
         double* Bj = Bs + (int64_t)(J * TS + kc) * QB + 16 * h;
@@ -325,6 +329,7 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
             if (h == 0) sTau[c] = tau;
           }
           wave_sync();
+          if (lane == 0) __hip_atomic_store(&s_done, c + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
           if (tau != 0.0) {
             double v[16];
 #pragma unroll
@@ -343,10 +348,14 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
           Bj[q] = 0.0;
         }
       }
-      __syncthreads();
-      // the reflectors applied to the tiles right of J in the envelope, one
-      // wave per tile with the same lane map
-      for (int a = wave; a < nr; a += QR_THREADS / 64) {
+      // the reflectors applied to the tiles right of J in the envelope, as they
+      // come, one wave per tile with the same lane map
+      int have = wave == 0 ? TS : 0;
+      while (true) {
+        int a = 0;
+        if (lane == 0) a = atomicAdd(&s_next, 1);
+        a = __builtin_amdgcn_readfirstlane(a);
+        if (a >= nr) break;
         const int K = sRows[a];
         double* Rjk = rtile(J, K);
         double* Bk = Bs + (int64_t)(K * TS + kc) * QB + 16 * h;
@@ -358,6 +367,11 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
         }
 #pragma unroll
         for (int c = 0; c < TS; ++c) {
+          // the panel's wave waits for nobody, so this ends
+          while (have <= c) {
+            have = __hip_atomic_load(&s_done, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (have <= c) __builtin_amdgcn_s_sleep(1);
+          }
           const double tau = sTau[c];
           if (tau == 0.0) continue;
           const int hc = c >> 4, ic = c & 15;
@@ -376,17 +390,21 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
           Bk[q] = b[q];
           nz |= b[q] != 0.0;
         }
-        if (nz) sNZ[a] = 1;
+        const unsigned long long any = __ballot(nz);
+        if (lane == 0) sNZ[a] = any != 0;
       }
       __syncthreads();
       // a tile joins the block only if some row of it is nonzero there:
       // exact zeros stay zeros, and the block ends where its rows do
-      if (tid == 0)
+      if (tid == 0) {
         for (int a = 0; a < nr; ++a)
           if (sNZ[a]) {
             sGen[sRows[a]] = gen;
             s_jmax = max(s_jmax, sRows[a]);
           }
+        s_done = 0;
+        s_next = 0;
+      }
       __syncthreads();
       ++J;
     }
