@@ -330,10 +330,10 @@ lsq2l_status lsq2l_autotune(lsq2l_handle h, int32_t reps, int32_t* lanes);
  * each column in ascending order.  In: m, n, nnz < 2^31; rowptr (m + 1, int32),
  * colind (nnz), vals (nnz, may be NULL).  Out: trowptr (n + 1), trow (nnz,
  * row index of each entry of A^T), tvals (nnz, may be NULL), tperm (nnz, may
- * be NULL: the index in A of each entry of A^T).  Runs a counting sort
- * (column histogram, exclusive scan, scatter, per-column ordering) on
- * `hip_stream`; its work arrays (n + 1 counters and the scan's block sums)
- * are allocated and freed inside the call.  EINVAL on bad sizes or NULL
+ * be NULL: the index in A of each entry of A^T).  Runs a stable radix sort by
+ * column on `hip_stream`; its work arrays (up to 28 bytes per entry, and the
+ * digit counts) come from the library's cache of device memory and go back to
+ * it inside the call (lsq2l_release_cache frees them).  EINVAL on bad sizes or NULL
  * required pointers.  Column indices must lie in [0, n).
  */
 lsq2l_status lsq2l_transpose(int32_t m, int32_t n, int32_t nnz, const int32_t* rowptr,

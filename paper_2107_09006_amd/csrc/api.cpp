@@ -791,10 +791,9 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   c->s_total_fac = ftiles * TT;
   c->s_total_dinv = dtiles * TT;
   c->s_total_tiles = dtiles;
-  c->s_total_np = 0;
   DevPlan& Ps = c->Ps;
   Ps.max_np = 0;
-  for (const SubDesc& d : s) { c->s_total_np += d.np; Ps.max_np = std::max(Ps.max_np, (int)d.np); }
+  for (const SubDesc& d : s) Ps.max_np = std::max(Ps.max_np, (int)d.np);
   std::vector<int32_t> order(nsub);
   for (int i = 0; i < nsub; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return tiles[x] > tiles[y]; });

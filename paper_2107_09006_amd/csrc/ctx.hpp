@@ -118,7 +118,7 @@ struct lsq2l_ctx {
   // in the layout Ps: sfac / sdinv (FP64 path), fac32 / dinv32 (mixed path).
   bool solve_plan = false;
   lsq2l::DevPlan Ps;
-  int64_t s_total_fac = 0, s_total_dinv = 0, s_total_np = 0, s_total_tiles = 0;
+  int64_t s_total_fac = 0, s_total_dinv = 0, s_total_tiles = 0;
   lsq2l::SolveStream ss;      // what the local solves read, laid out from those factors
   // candidate global-order layouts of the setup (solve_layout_begin): host
   // copy, device copy, position map and the envelope the assembly finds
