@@ -39,14 +39,14 @@ HBM_PEAK_GBS = 8000.0
 CALIB_BYTES = 1 << 30          # plain device copy used to calibrate HBM counters
 
 # HBM traffic of one launch of the dominant kernel (the FP64 local solves,
-# k_local_solve_pipe<double>) on the default workload, from rocprofv3 --pmc
+# k_local_solve_stream<double>) on the default workload, from rocprofv3 --pmc
 # FETCH_SIZE and WRITE_SIZE runs of this script, each scaled by the same
-# counter's reading for the calibration copy (profiles/local_solve_banded_batch_64.md).
+# counter's reading for the calibration copy (profiles/setup_and_solve.md).
 # It describes the kernel source whose SHA-256 is given; for any other source
 # the figure is reported as null.
 TRAFFIC = {"source": "paper_2107_09006_amd/csrc/k_solve.hip",
-           "sha256": "3730a371a904e7e39a98b740966380b5f5a7f7a6c63f2243ecf41d40cc648404",
-           "bytes": 2107597.3 * 1024 * 2.0 + 24834.91 * 1024 * 1.0}
+           "sha256": "5f47e9d5b7f321ff5f37787ec9bcd15ae48e7cfb9e5e4db5c722b608823f6b6e",
+           "bytes": 1488678.12 * 1024 * 2.0 + 30789.94 * 1024 * 1.0}
 
 
 def log(*a):
@@ -296,7 +296,7 @@ def main():
     stored = kern64.get("local_solve_stored")
     roofline = None
     if dom:
-        roofline = {"kernel": "k_local_solve_pipe<double>", "bound": "hbm",
+        roofline = {"kernel": "k_local_solve_stream<double>", "bound": "hbm",
                     "achieved": round(dom["GBs"], 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(dom["GBs"] / HBM_PEAK_GBS, 4),
                     "traffic": measured_traffic() if args.workload == "banded_batch_64" else None,
