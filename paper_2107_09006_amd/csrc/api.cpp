@@ -953,6 +953,10 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   if (!pat.started) {
     const lsq2l_status s = plan_build_device(c, nparts, seg_of_part, owner, work, D);
     if (s == LSQ2L_EINVAL || s == LSQ2L_EHIP) return s;
+    if (s != LSQ2L_OK) {                  // no work space: the host plans, with a clean slate
+      (void)hipGetLastError();
+      g_err.clear();
+    }
   }
   RowOrder ro;
   JoiningThread ro_thread;
