@@ -788,6 +788,8 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   c->info.solve_permuted = permuted;
   if (!mixed && !qr && permuted == 0) return LSQ2L_OK;
   c->solve_plan = true;
+  c->solve_tiles = tiles;
+  for (const SubDesc& d : s) c->solve_np.push_back(d.np);
   c->s_total_fac = ftiles * TT;
   c->s_total_dinv = dtiles * TT;
   c->s_total_tiles = dtiles;
@@ -836,6 +838,12 @@ lsq2l_status solve_stream(lsq2l_ctx* c, hipStream_t st) {
     TRY(c->dalloc(&S.pos[dir], 4 * tiles));
     TRY(c->dalloc(&S.desc[dir], 4 * (tiles + 1)));
   }
+  if (!own)
+    for (int i = 0; i < c->nsub; ++i) {
+      const int64_t end = i + 1 < c->nsub ? c->H.subs[i + 1].fac_off : c->H.total_fac;
+      c->solve_tiles.push_back((end - c->H.subs[i].fac_off) / TT);
+      c->solve_np.push_back(c->H.subs[i].np);
+    }
   TRY(c->dalloc(&S.far0, SOLVE_FAR_INTS * (int64_t)c->nsub));
   TRY(c->dalloc(&S.scol, locs));
   TRY(c->dalloc(&S.sscale, locs));
@@ -1944,18 +1952,26 @@ lsq2l_status lsq2l_time_kernel(lsq2l_handle c, int32_t kernel, int32_t reps, dou
     case 0: *bytes = 12.0 * nnz + 4.0 * (m + 1) + 8.0 * n + 8.0 * m; break;
     case 1: *bytes = 12.0 * nnz + 4.0 * (n + 1) + 8.0 * m + 8.0 * n; break;
     // the packed diagonal inverses twice, the chain tiles and slabs of both
-    // sweeps, their tables, and the gather and result per local unknown
+    // sweeps with their tables; of a subdomain beyond the streams, its stored
+    // tiles in both sweeps (the diagonal ones as inverses); and the gather and
+    // result per local unknown
     case 2: {
       std::vector<int32_t> far((size_t)c->nsub * SOLVE_FAR_INTS);
       LSQ2L_HIP_TRY(hipMemcpyAsync(far.data(), c->ss.far0, far.size() * sizeof(int32_t),
                                    hipMemcpyDeviceToHost, c->st));
       LSQ2L_HIP_TRY(hipStreamSynchronize(c->st));
-      const double rows = (double)(c->solve_plan ? c->s_total_dinv : c->H.total_dinv) / TT;
-      double slabs = 0;
-      for (int i = 0; i < c->nsub; ++i)
-        for (int dir = 1; dir <= 2; ++dir) slabs += far[(size_t)i * SOLVE_FAR_INTS + dir * (SOLVE_FAR_INTS / 2) - 1];
-      *bytes = eb * (rows * 2.0 * (SOLVE_DPACK + TT) + slabs * TS * 8) + 4.0 * slabs +
-               (4.0 + 8.0 + 8.0 + 8.0 + 4.0 + 8.0) * rows * TS;
+      *bytes = 0.0;
+      for (int i = 0; i < c->nsub; ++i) {
+        const double np = c->solve_np[i], rows = np / TS;
+        if (c->solve_np[i] > local_solve_cap()) {
+          *bytes += 2.0 * eb * TT * (double)c->solve_tiles[i];
+        } else {
+          double slabs = 0;
+          for (int dir = 1; dir <= 2; ++dir) slabs += far[(size_t)i * SOLVE_FAR_INTS + dir * (SOLVE_FAR_INTS / 2) - 1];
+          *bytes += eb * (rows * 2.0 * (SOLVE_DPACK + TT) + slabs * TS * 8) + 4.0 * slabs;
+        }
+        *bytes += (4.0 + 8.0 + 8.0 + 8.0 + 4.0 + 8.0) * np;
+      }
       break;
     }
     // the algorithmic minimum: each sweep reads the nnz(L_i) entries of the

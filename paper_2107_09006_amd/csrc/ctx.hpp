@@ -119,6 +119,8 @@ struct lsq2l_ctx {
   bool solve_plan = false;
   lsq2l::DevPlan Ps;
   int64_t s_total_fac = 0, s_total_dinv = 0, s_total_tiles = 0;
+  std::vector<int64_t> solve_tiles;   // per subdomain: stored tiles and padded size of
+  std::vector<int32_t> solve_np;      // the layout that the local solves read
   lsq2l::SolveStream ss;      // what the local solves read, laid out from those factors
   // candidate global-order layouts of the setup (solve_layout_begin): host
   // copy, device copy, position map and the envelope the assembly finds
