@@ -809,7 +809,7 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   TRY(c->dalloc(&Ps.sperm, std::max<int64_t>(lo, 1)));
   launch_fill_i32(st, lo, -1, Ps.sperm);
   launch_solve_perm(st, nsub, c->P, Ps.subs, inv, Ps.sperm);
-  if (Ps.max_np > local_solve_cap()) TRY(c->dalloc(&Ps.yscratch, std::max<int64_t>(lo, 1)));
+  if (Ps.max_np > local_solve_cap(mixed)) TRY(c->dalloc(&Ps.yscratch, std::max<int64_t>(lo, 1)));
   TRY(c->dalloc(s64, std::max<int64_t>(c->s_total_fac, 1)));
   if (qr) LSQ2L_HIP_TRY(hipMemsetAsync(*s64, 0, c->s_total_fac * sizeof(double), st));
   else launch_gather_solve(st, nsub, c->P, Ps, c->fac, *s64);
@@ -830,6 +830,7 @@ lsq2l_status solve_stream(lsq2l_ctx* c, hipStream_t st) {
   TRY(c->dalloc(&f, (int64_t)((tiles + 1) * TT * eb)));
   TRY(c->dalloc(&b, (int64_t)((tiles + 1) * TT * eb)));
   TRY(c->dalloc(&dp, (int64_t)(rows * SOLVE_DPACK * eb)));
+  S.cap = local_solve_cap(c->opt.precision == LSQ2L_MIXED);
   S.fwd = f;
   S.bwd = b;
   S.dpack = dp;
@@ -1963,7 +1964,7 @@ lsq2l_status lsq2l_time_kernel(lsq2l_handle c, int32_t kernel, int32_t reps, dou
       *bytes = 0.0;
       for (int i = 0; i < c->nsub; ++i) {
         const double np = c->solve_np[i], rows = np / TS;
-        if (c->solve_np[i] > local_solve_cap()) {
+        if (c->solve_np[i] > c->ss.cap) {
           *bytes += 2.0 * eb * TT * (double)c->solve_tiles[i];
         } else {
           double slabs = 0;

@@ -52,9 +52,15 @@ constexpr int CHAIN = 2;                     // waves that take the chain tiles 
 constexpr int HELPERS = SOLVE_WAVES - CHAIN; // waves that take the slabs
 constexpr int DPACK = SOLVE_DPACK;           // entries of a packed D_I: ten 8 x 8 blocks
 static_assert(SOLVE_FAR_INTS == 2 * (HELPERS + 1), "far0 entries");
-// Largest subdomain whose local vector fits in LDS beside the tables (FP64:
-// 148 of 160 KB); larger ones are solved in global memory (k_local_solve).
-constexpr int SCAP = 18944;
+// Largest subdomain that the streams solve; larger ones are solved in global
+// memory (k_local_solve).  FP64 factors: where the local vector fits in LDS beside
+// the tables (148 of 160 KB).  FP32 factors: 12,544 unknowns.  The streams hold
+// the vector and its sums in the factors' type, k_local_solve holds them in double:
+// M r on one banded subdomain of 13,000 / 18,944 unknowns is off by 1.15e-7 /
+// 1.24e-7 with it, by 1.27e-7 / 1.42e-7 with streams (which take 0.30 / 0.43 ms
+// instead of 1.4 / 2.4).
+template <typename T> constexpr int SCAP_OF = sizeof(T) == 8 ? 18944 : 12544;
+constexpr int SCAP = SCAP_OF<double>;
 constexpr int SCAP_TILES = SCAP / TS;
 
 // x + x of the lane 8 / 16 away within its row of 16 / pair of rows
@@ -106,7 +112,7 @@ k_stream_layout(const SubDesc* __restrict__ subs, const int32_t* __restrict__ ti
   __shared__ int f8[4 * SCAP_TILES];
   __shared__ int cnt[SCAP_TILES], off[HELPERS][SCAP_TILES], wb[HELPERS + 1];
   const SubDesc d = subs[blockIdx.x];
-  if (d.np > SCAP) return;
+  if (d.np > S.cap) return;
   const int nt = d.ntiles, tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int32_t* F = tileF + d.tile_base;
   const int64_t* O = tileOff + d.tile_base;
@@ -188,7 +194,7 @@ k_stream_pack(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
   using Map = StreamMap<T>;
   __shared__ T sL[4][TS * LDT], sD[4][TS * LDT];
   const SubDesc d = subs[blockIdx.x];
-  if (d.np > SCAP) return;
+  if (d.np > S.cap) return;
   const int nt = d.ntiles, lane = threadIdx.x % 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
   const int li = lane % 16, lk = lane / 16;
@@ -528,7 +534,7 @@ k_local_solve_stream(const SubDesc* __restrict__ subs, SolveStream S, const T* _
                      const int32_t* __restrict__ sperm) {
   extern __shared__ __align__(16) unsigned char smem[];
   const SubDesc d = subs[blockIdx.x];
-  if (d.np > SCAP) return;                       // k_local_solve
+  if (d.np > S.cap) return;                       // k_local_solve
   const int nt = d.ntiles, tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   T* y = reinterpret_cast<T*>(smem);
@@ -564,7 +570,7 @@ static size_t stream_lds_bytes(int np, size_t elem) {
 }
 static_assert(SCAP * 8 + 2 * HELPERS * TS * 8 + 2 * SCAP_TILES * 2 <= 160 * 1024, "LDS of the local solve");
 
-// Subdomains above SCAP local unknowns: forward and backward substitution
+// Subdomains above S.cap local unknowns: forward and backward substitution
 // by tile rows with y in global memory, workgroup per subdomain, 32 rows of
 // threads each summing every eighth tile of a row (fixed order), the
 // diagonal blocks applied through their inverses.
@@ -582,7 +588,7 @@ k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
   const int64_t* off = tileOff + d.tile_base;
   const T* A = fac + d.fac_off;
   const T* Di = dinv + d.dinv_off;
-  if (d.np <= SCAP) return;                 // done by k_local_solve_stream
+  if (d.np <= S.cap) return;                // done by k_local_solve_stream
   const int32_t* sp = sperm ? sperm + d.loc_off : nullptr;
   // y in global memory: in place in loc, or, for a permuted layout, in the
   // subdomain's slice of scratch
@@ -646,7 +652,7 @@ k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-int local_solve_cap() { return SCAP; }
+int local_solve_cap(bool f32) { return f32 ? SCAP_OF<float> : SCAP_OF<double>; }
 
 void launch_stream_layout(hipStream_t st, int nsub, const DevPlan& P, const int32_t* F8,
                           const SubDesc* gsub, int64_t tiles, const SolveStream& S) {
@@ -673,10 +679,10 @@ template void launch_stream_pack<float>(hipStream_t, int, const DevPlan&, const 
 template <typename T>
 void launch_local_solve(hipStream_t st, int nsub, const DevPlan& P, const SolveStream& S, const T* fac,
                         const T* dinv, const double* r, double* loc) {
-  const size_t lds = stream_lds_bytes(std::min(P.max_np, SCAP), sizeof(T));
+  const size_t lds = stream_lds_bytes(std::min(P.max_np, S.cap), sizeof(T));
   k_local_solve_stream<T><<<nsub, 64 * SOLVE_WAVES, lds, st>>>(P.heavy(), S, (const T*)S.fwd, (const T*)S.bwd,
                                                   (const T*)S.dpack, r, loc, P.sperm);
-  if (P.max_np > SCAP)
+  if (P.max_np > S.cap)
     k_local_solve<T><<<nsub, 256, 0, st>>>(P.subs, P.tileF, P.tileOff, fac, dinv, S, r, loc, P.sperm,
                                            P.yscratch);
 }
@@ -688,11 +694,11 @@ template void launch_local_solve<float>(hipStream_t, int, const DevPlan&, const 
 hipError_t local_solve_configure() {
   hipError_t e = hipFuncSetAttribute((const void*)k_local_solve_stream<double>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)stream_lds_bytes(SCAP, sizeof(double)));
+                                     (int)stream_lds_bytes(SCAP_OF<double>, sizeof(double)));
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void*)k_local_solve_stream<float>,
                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)stream_lds_bytes(SCAP, sizeof(float)));
+                            (int)stream_lds_bytes(SCAP_OF<float>, sizeof(float)));
   return e;
 }
 

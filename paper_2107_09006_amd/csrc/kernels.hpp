@@ -48,6 +48,7 @@ constexpr int SOLVE_FAR_INTS = 14;    // entries of SolveStream::far0 per subdom
 // What the local solves read (k_solve.hip): the streams of both sweeps and
 // the packed diagonal inverses, in the type of the factors, with their tables
 struct SolveStream {
+  int cap = 0;                            // largest padded subdomain that they solve
   void *fwd = nullptr, *bwd = nullptr;    // as many entries as the factor's envelope, and a tile
   void* dpack = nullptr;                  // SOLVE_DPACK entries per diagonal tile
   uint16_t* nfar[2] = {nullptr, nullptr}; // slabs of every step (tile_base + step)
@@ -308,7 +309,7 @@ void launch_stream_pack(hipStream_t st, int nsub, const DevPlan& P, const T* fac
 template <typename T>
 void launch_local_solve(hipStream_t st, int nsub, const DevPlan& P, const SolveStream& S, const T* fac,
                         const T* dinv, const double* r, double* loc);
-int local_solve_cap();    // largest subdomain whose local vector is held in LDS
+int local_solve_cap(bool f32);    // largest subdomain that the streams solve (FP32 or FP64 factors)
 // allows the streaming local solve its dynamic LDS (once per process)
 hipError_t local_solve_configure();
 // restricted: each column takes its owner's interior value only (R_i^T D_i, eq. RAS)
