@@ -24,14 +24,14 @@ inline double ms_since(clk::time_point t0) {
 }
 
 // Device blocks of destroyed handles, kept for later handles on the same
-// device (api.cpp).
+// device (blocks.cpp).
 void* cache_take(size_t bytes, int dev, size_t* got);
 // a block of at least the given size on the current device, from the cache or new
 lsq2l_status device_block(void** p, size_t bytes, size_t* got, int* dev);
 void cache_give(void* p, size_t bytes, int dev);
 void cache_release();
 
-// Pinned host buffers kept for later setups (api.cpp).
+// Pinned host buffers kept for later setups (blocks.cpp).
 void* pinned_take(size_t bytes, size_t* got);
 void pinned_give(void* p, size_t bytes);
 void pinned_release();
@@ -190,7 +190,11 @@ struct lsq2l_ctx {
   lsq2l_status halloc(T** ptr, int64_t count) {
     void* v = nullptr;
     hipError_t e = hipHostMalloc(&v, (size_t)std::max<int64_t>(count, 1) * sizeof(T), hipHostMallocDefault);
-    if (e != hipSuccess) { lsq2l::set_error("pinned host allocation failed"); return LSQ2L_ENOMEM; }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      lsq2l::set_error("pinned host allocation failed");
+      return LSQ2L_ENOMEM;
+    }
     host_allocs.push_back(v);
     *ptr = (T*)v;
     return LSQ2L_OK;
