@@ -787,12 +787,18 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   Scratch work(st);                // given back with the setup
   int2* owner = nullptr;
   TRY(work.alloc(&owner, nnz));
+  Scratch pairs(st);               // read by the maps thread, which ends before
   DevicePlan D;
   if (!pat.started) {
-    const lsq2l_status s = plan_build_device(c, nparts, seg_of_part, owner, work, D);
+    const lsq2l_ctx::Mark before = c->mark();
+    const lsq2l_status s = plan_build_device(c, nparts, seg_of_part, owner, pairs, D);
     if (s == LSQ2L_EINVAL || s == LSQ2L_EHIP) return s;
-    if (s != LSQ2L_OK) {                  // no work space: the host plans, with a clean slate
+    if (!D.done) {                        // the host plans, with a clean slate
       g_err.clear();
+      LSQ2L_HIP_TRY(hipStreamSynchronize(st));
+      pairs.release();
+      c->rollback(before);
+      c->H = HostPlan{};
     }
   }
   RowOrder ro;

@@ -186,6 +186,19 @@ struct lsq2l_ctx {
     *ptr = (T*)v;
     return LSQ2L_OK;
   }
+  // Device memory allocated since a mark goes back (the caller has synchronized
+  // the work on it).
+  struct Mark { size_t blocks; char* cur; size_t used; };
+  Mark mark() const { return {dev_allocs.size(), arena_cur, arena_used}; }
+  void rollback(const Mark& k) {
+    while (dev_allocs.size() > k.blocks) {
+      const DevBlock b = dev_allocs.back();
+      dev_allocs.pop_back();
+      lsq2l::cache_give(b.p, b.bytes, b.dev);
+    }
+    arena_cur = k.cur;
+    arena_used = k.used;
+  }
   template <typename T>
   lsq2l_status halloc(T** ptr, int64_t count) {
     void* v = nullptr;

@@ -65,6 +65,20 @@ int main() {
   cache_give(b, nb, dev);
   cache_release();
   CHECK(live.empty() && in_use == 0, "everything given back");
+  // a handle's memory back to a mark: own blocks, arena chunks begun since, and
+  // the place in the chunk that was open
+  lsq2l_ctx& h = *new lsq2l_ctx();
+  int32_t *x = nullptr, *y = nullptr, *z = nullptr, *again = nullptr;
+  CHECK(h.dalloc(&x, 1000) == LSQ2L_OK, "from the arena");
+  const size_t at_mark = in_use;
+  const lsq2l_ctx::Mark k = h.mark();
+  CHECK(h.dalloc(&y, 1000) == LSQ2L_OK && h.dalloc(&z, (int64_t)100 * MiB / 4) == LSQ2L_OK, "own block");
+  for (int q = 0; q < 6; ++q) CHECK(h.dalloc(&z, (int64_t)60 * MiB / 4) == LSQ2L_OK, "a second chunk");
+  CHECK(in_use > at_mark + 100 * MiB + 256 * MiB, "a block and a chunk more");
+  h.rollback(k);
+  cache_release();
+  CHECK(in_use == at_mark, "given back to the mark");
+  CHECK(h.dalloc(&again, 1000) == LSQ2L_OK && again == y, "the arena goes on at the mark");
   printf("OK\n");
   return 0;
 }
