@@ -767,12 +767,13 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   // --- transpose and index sets
   // A^T on the device, while the host plans from A's pattern
   char* temp = nullptr;
-  const size_t tb = transpose_temp_bytes(nnz, n);
+  size_t tb = 0;
+  Scratch sort(st);                // given back when A^T is there
   TRY(c->dalloc(&c->M.trowptr, (int64_t)n + 1));
   TRY(c->dalloc(&c->M.trow, nnz));
   TRY(c->dalloc(&c->M.tperm, nnz));
   TRY(c->dalloc(&c->M.tvals, nnz));
-  TRY(c->dalloc(&temp, (int64_t)std::max<size_t>(tb, 1)));
+  TRY(transpose_space(sort, nnz, n, &temp, &tb));
   LSQ2L_HIP_TRY(launch_transpose(st, m, n, nnz, c->M.rowptr, c->M.colind, c->M.vals, c->M.trowptr,
                                  c->M.trow, c->M.tvals, c->M.tperm, temp, tb));
   TRY(c->dalloc(&c->M.blk, spmv_table_len(nnz)));
@@ -861,6 +862,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
     LSQ2L_HIP_TRY(conf);
   }
   LSQ2L_HIP_TRY(hipStreamSynchronize(st));
+  sort.release();
   c->info.t_plan_ms = ms_since(t0);
   // --- local matrices
   t0 = clk::now();
@@ -1301,6 +1303,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
       TRY(c->upload(&c->mi_perm, ro.perm));
       TRY(c->upload(&Mi.rowptr, ro.prp));
     }
+    TRY(transpose_space(sort, nnz, n, &temp, &tb));
     launch_permute_rows(st, m, c->mi_perm, c->M.rowptr, c->M.colind, c->M.vals, Mi.rowptr, Mi.colind, Mi.vals);
     LSQ2L_HIP_TRY(launch_transpose(st, m, n, nnz, Mi.rowptr, Mi.colind, Mi.vals, Mi.trowptr, Mi.trow,
                                    Mi.tvals, Mi.tperm, temp, tb));
@@ -1889,7 +1892,7 @@ lsq2l_status lsq2l_transpose(int32_t m, int32_t n, int32_t nnz, const int32_t* r
     return LSQ2L_EINVAL;
   }
   const hipStream_t st = (hipStream_t)hip_stream;
-  const size_t tb = transpose_temp_bytes(nnz, n);
+  size_t tb = transpose_temp_bytes(nnz, n);
   // the sort carries the permutation; a caller that does not want it gets
   // a temporary one.  The last 256 bytes hold the column check flag.
   const size_t perm_bytes = tperm ? 0 : ((size_t)nnz * sizeof(int32_t) + 255) / 256 * 256;
@@ -1898,7 +1901,11 @@ lsq2l_status lsq2l_transpose(int32_t m, int32_t n, int32_t nnz, const int32_t* r
   size_t held = 0;
   int dev = 0;
   void* temp = nullptr;
-  if (device_block(&temp, tb + perm_bytes + 256, &held, &dev) != LSQ2L_OK) return LSQ2L_EHIP;
+  if (device_block(&temp, tb + perm_bytes + 256, &held, &dev) != LSQ2L_OK) {
+    tb = transpose_temp_least(nnz, n);
+    if (device_block(&temp, tb + perm_bytes + 256, &held, &dev) != LSQ2L_OK) return LSQ2L_EHIP;
+    g_err.clear();
+  }
   int32_t* perm = tperm ? tperm : (int32_t*)((char*)temp + tb);
   int32_t* flag = (int32_t*)((char*)temp + tb + perm_bytes);
   int32_t hflag = 0;

@@ -410,6 +410,7 @@ static size_t temp_bytes_for(int64_t nnz, int32_t n, int width, bool carry) {
 }
 
 size_t transpose_temp_bytes(int64_t nnz, int32_t n) { return temp_bytes_for(nnz, n, RS_BITS, true); }
+size_t transpose_temp_least(int64_t nnz, int32_t n) { return temp_bytes_for(nnz, n, RS_NARROW, false); }
 
 // With less than transpose_temp_bytes, rows and values are gathered after the
 // sort, and with less room still the digits are RS_NARROW bits wide (an

@@ -83,13 +83,14 @@ struct DevCoarse {            // coarse space and coarse operator
 constexpr int ESYM_ROWTILES = 8;
 
 // --- device transpose of A (hand-written radix sort) ------------------------
-size_t transpose_temp_bytes(int64_t nnz, int32_t n);
+size_t transpose_temp_bytes(int64_t nnz, int32_t n);   // 24 bytes per entry (16 with one pass), and the histogram
+size_t transpose_temp_least(int64_t nnz, int32_t n);   // 8 bytes per entry (0 with one pass), and the histogram
 void launch_permute_rows(hipStream_t st, int32_t m, const int32_t* perm, const int32_t* rowptr,
                          const int32_t* colind, const double* vals, const int32_t* prowptr,
                          int32_t* pcolind, double* pvals);
 // trowptr (n + 1), trow and tperm (nnz) written; tvals written if not null
 // (vals must then be given); temp holds transpose_temp_bytes(nnz, n) bytes, or
-// fewer if they are enough for the narrow digits
+// fewer, down to transpose_temp_least(nnz, n)
 hipError_t launch_transpose(hipStream_t st, int32_t m, int32_t n, int64_t nnz, const int32_t* rowptr,
                             const int32_t* colind, const double* vals, int32_t* trowptr,
                             int32_t* trow, double* tvals, int32_t* tperm, void* temp,

@@ -30,6 +30,16 @@ struct Scratch {
   }
 };
 
+// Work space of a transpose of nnz entries and n columns: what carries rows and
+// values through the sort, or where that cannot be had the least (a third of it;
+// rows and values are gathered then, see launch_transpose)
+inline lsq2l_status transpose_space(Scratch& s, int64_t nnz, int32_t n, char** temp, size_t* bytes) {
+  *bytes = transpose_temp_bytes(nnz, n);
+  if (s.alloc(temp, (int64_t)*bytes) == LSQ2L_OK) return LSQ2L_OK;
+  *bytes = transpose_temp_least(nnz, n);
+  return s.alloc(temp, (int64_t)*bytes);
+}
+
 // From this many entries on the device plans: some thirty launches and six
 // reads of counts, 0.6 ms at 9,000 entries (host 0.55), 0.8 at 2.7e5 (2.1),
 // 1.2 at 3.8e6 (6.9), 5.5 at 3.3e7 (16).
