@@ -1358,6 +1358,17 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   TRY(krylov_alloc(c));
   TRY(finish_solve_factors());
   LSQ2L_HIP_TRY(hipStreamSynchronize(st));
+  // The streams hold what the local solves read, and the coarse space is there:
+  // the factors are read no more, unless a subdomain lies beyond the streams
+  if (*std::max_element(c->solve_np.begin(), c->solve_np.end()) <= c->ss.cap) {
+    c->give_back(c->fac);
+    c->give_back(c->dinv);
+    c->give_back(s64);
+    c->give_back(c->sdinv);
+    c->give_back(c->fac32);
+    c->give_back(c->dinv32);
+    c->sfac = nullptr;
+  }
   c->release_staged();
   if (c->opt.autotune) TRY(autotune_spmv(c, 10));
   // --- info

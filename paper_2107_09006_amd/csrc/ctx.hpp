@@ -153,7 +153,7 @@ struct lsq2l_ctx {
   int max_p = 0;
   int64_t fac_nnz_min = -1;       // symbolic nnz(L) under a fill-reducing order (lazy)
   lsq2l_setup_info info{};
-  struct DevBlock { void* p; size_t bytes; int dev; };
+  struct DevBlock { void* p; size_t bytes; int dev; bool chunk = false; };   // chunk: of the arena
   std::vector<DevBlock> dev_allocs;
   std::vector<void*> host_allocs;
 
@@ -177,6 +177,7 @@ struct lsq2l_ctx {
       if (!arena_cur || arena_used + bytes > ARENA_CHUNK) {
         lsq2l_status s = raw_alloc(&v, ARENA_CHUNK);
         if (s != LSQ2L_OK) return s;
+        dev_allocs.back().chunk = true;
         arena_cur = (char*)v;
         arena_used = 0;
       }
@@ -198,6 +199,18 @@ struct lsq2l_ctx {
     }
     arena_cur = k.cur;
     arena_used = k.used;
+  }
+  // An array that nothing reads any more goes back, if it is a block of its own
+  // (the caller has synchronized the work on it)
+  template <typename T>
+  void give_back(T*& ptr) {
+    for (size_t k = 0; k < dev_allocs.size(); ++k)
+      if (dev_allocs[k].p == (void*)ptr && !dev_allocs[k].chunk) {
+        lsq2l::cache_give(dev_allocs[k].p, dev_allocs[k].bytes, dev_allocs[k].dev);
+        dev_allocs.erase(dev_allocs.begin() + k);
+        break;
+      }
+    ptr = nullptr;
   }
   template <typename T>
   lsq2l_status halloc(T** ptr, int64_t count) {

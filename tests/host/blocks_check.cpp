@@ -79,6 +79,17 @@ int main() {
   cache_release();
   CHECK(in_use == at_mark, "given back to the mark");
   CHECK(h.dalloc(&again, 1000) == LSQ2L_OK && again == y, "the arena goes on at the mark");
+  // an array of its own goes back alone; one at the start of a chunk does not
+  // take the chunk with it
+  int32_t *own = nullptr, *first = nullptr;
+  CHECK(h.dalloc(&own, (int64_t)100 * MiB / 4) == LSQ2L_OK, "own block");
+  for (int q = 0; q < 5; ++q) CHECK(h.dalloc(&first, (int64_t)60 * MiB / 4) == LSQ2L_OK, "a chunk's pieces");
+  CHECK(live.count(first) == 1, "the last piece starts a chunk");
+  const size_t with_own = in_use;
+  h.give_back(own);
+  h.give_back(first);
+  cache_release();
+  CHECK(!own && !first && with_own - in_use >= 100 * MiB && with_own - in_use < 200 * MiB, "one block given back");
   printf("OK\n");
   return 0;
 }

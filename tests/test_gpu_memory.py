@@ -77,3 +77,25 @@ def test_handle_keeps_no_work_space():
     held = before - torch.cuda.mem_get_info()[0]
     s.close()
     assert held <= 28 * p.nnz * 9 / 8 + (256 + 64) * MiB
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_handle_keeps_one_copy_of_the_factors(precision):
+    """What the local solves read (two sweeps of at most factor_tiles tiles each;
+    blocks are up to an eighth larger) and A stay; the factors that they are laid
+    out from do not.  512 MiB: two chunks for the arrays of up to 64 MiB."""
+    import torch
+    import paper_2107_09006_amd as L
+    from workloads import generators as W
+    p = W.random_banded(160000, 320000, 40, seed=9, half_width=200)
+    lib = L.load_library()
+    lib.lsq2l_release_cache()
+    before = torch.cuda.mem_get_info()[0]
+    s = L.solver_from_problem(p, variant=L.ONE_LEVEL, precision=L.FP64 if precision == "fp64" else L.MIXED)
+    lib.lsq2l_release_cache()
+    held = before - torch.cuda.mem_get_info()[0]
+    tile = 1024 * (8 if precision == "fp64" else 4)
+    two = 2 * tile * s.info()["factor_tiles"]
+    assert two > 512 * MiB
+    s.close()
+    assert held <= (two + 28 * p.nnz) * 9 / 8 + 512 * MiB
