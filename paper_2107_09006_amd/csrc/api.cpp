@@ -77,7 +77,7 @@ void spmv_A(lsq2l_ctx* c, const double* x, double* y) {
   launch_spmv(c->st, c->M.m, c->M.rowptr, c->M.colind, c->M.vals, x, y, c->M.spmv_group, c->M.nnz, c->M.blk);
 }
 void spmv_AT(lsq2l_ctx* c, const double* y, double* x) {
-  if (c->row_perm && c->Mi.spmvt_group <= 0) {
+  if (c->mi_y && c->Mi.spmvt_group <= 0) {
     launch_gather(c->st, c->M.m, c->mi_perm, y, c->mi_y);
     spmv_it_AT(c, c->mi_y, x);
     return;
@@ -645,21 +645,36 @@ lsq2l_status solve_layout(lsq2l_ctx* c, double** s64) {
   return LSQ2L_OK;
 }
 
-// The streams of the local solves in the layout P: space, tables and gather
-// maps, enqueued on st (the entries follow the factors, pack_solve_stream).
+// The gather maps of the local solves in their layout, and its sizes
+lsq2l_status solve_cols(lsq2l_ctx* c, hipStream_t st) {
+  const bool own = c->solve_plan;
+  const int64_t locs = own ? c->sl_loc : c->H.total_loc;
+  SolveStream& S = c->ss;
+  if (!own)
+    for (int i = 0; i < c->nsub; ++i) {
+      const int64_t end = i + 1 < c->nsub ? c->H.subs[i + 1].fac_off : c->H.total_fac;
+      c->solve_tiles.push_back((end - c->H.subs[i].fac_off) / TT);
+      c->solve_np.push_back(c->H.subs[i].np);
+    }
+  TRY(c->dalloc(&S.scol, locs));
+  TRY(c->dalloc(&S.sscale, locs));
+  launch_solve_cols(st, c->nsub, c->P, own ? c->Ps : c->P, c->scale, S);
+  return LSQ2L_OK;
+}
+
+// The streams of the local solves: space and tables, enqueued on st (the
+// entries follow the factors, pack_solve_stream).
 lsq2l_status solve_stream(lsq2l_ctx* c, hipStream_t st) {
   const bool own = c->solve_plan;
   const DevPlan& Lay = own ? c->Ps : c->P;
   SolveStream& S = c->ss;
   const int64_t tiles = (own ? c->s_total_fac : c->H.total_fac) / TT;
   const int64_t rows = (own ? c->s_total_dinv : c->H.total_dinv) / TT;
-  const int64_t locs = own ? c->sl_loc : c->H.total_loc;
   const size_t eb = c->opt.precision == LSQ2L_MIXED ? sizeof(float) : sizeof(double);
   char *f = nullptr, *b = nullptr, *dp = nullptr;
   TRY(c->dalloc(&f, (int64_t)((tiles + 1) * TT * eb)));
   TRY(c->dalloc(&b, (int64_t)((tiles + 1) * TT * eb)));
   TRY(c->dalloc(&dp, (int64_t)(rows * SOLVE_DPACK * eb)));
-  S.cap = local_solve_cap(c->opt.precision == LSQ2L_MIXED);
   S.fwd = f;
   S.bwd = b;
   S.dpack = dp;
@@ -668,17 +683,9 @@ lsq2l_status solve_stream(lsq2l_ctx* c, hipStream_t st) {
     TRY(c->dalloc(&S.pos[dir], 4 * tiles));
     TRY(c->dalloc(&S.desc[dir], 4 * (tiles + 1)));
   }
-  if (!own)
-    for (int i = 0; i < c->nsub; ++i) {
-      const int64_t end = i + 1 < c->nsub ? c->H.subs[i + 1].fac_off : c->H.total_fac;
-      c->solve_tiles.push_back((end - c->H.subs[i].fac_off) / TT);
-      c->solve_np.push_back(c->H.subs[i].np);
-    }
   TRY(c->dalloc(&S.far0, SOLVE_FAR_INTS * (int64_t)c->nsub));
-  TRY(c->dalloc(&S.scol, locs));
-  TRY(c->dalloc(&S.sscale, locs));
+  S.cap = local_solve_cap(c->opt.precision == LSQ2L_MIXED);
   launch_stream_layout(st, c->nsub, Lay, c->sl_F8, c->sl_dg, tiles, S);
-  launch_solve_cols(st, c->nsub, c->P, Lay, c->scale, S);
   return LSQ2L_OK;
 }
 
@@ -773,7 +780,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   TRY(c->dalloc(&c->M.trow, nnz));
   TRY(c->dalloc(&c->M.tperm, nnz));
   TRY(c->dalloc(&c->M.tvals, nnz));
-  TRY(transpose_space(sort, nnz, n, &temp, &tb));
+  TRY(transpose_space(sort, c->lean, nnz, n, &temp, &tb));
   LSQ2L_HIP_TRY(launch_transpose(st, m, n, nnz, c->M.rowptr, c->M.colind, c->M.vals, c->M.trowptr,
                                  c->M.trow, c->M.tvals, c->M.tperm, temp, tb));
   TRY(c->dalloc(&c->M.blk, spmv_table_len(nnz)));
@@ -785,9 +792,9 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   HostPlan& H = c->H;
   c->nsub = nparts;
   TRY(c->upload(&c->P.part, part));
-  Scratch work(st);                // given back with the setup
+  Scratch work(st);                // given back after the assembly
   int2* owner = nullptr;
-  TRY(work.alloc(&owner, nnz));
+  if (!c->lean) TRY(work.alloc(&owner, nnz));
   Scratch pairs(st);               // read by the maps thread, which ends before
   DevicePlan D;
   if (!pat.started) {
@@ -829,7 +836,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
     TRY(c->upload(&c->P.locown, H.locown));
     TRY(c->upload(&c->P.tileF, H.tileF));
     TRY(c->upload(&c->P.tileOff, H.tileOff));
-    launch_entry_owner(st, c->P, c->M, owner);
+    if (owner) launch_entry_owner(st, c->P, c->M, owner);
   }
   c->P.min_nG = INT32_MAX;
   for (const SubDesc& d : H.subs) {
@@ -926,6 +933,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   double* s64 = nullptr;
   TRY(solve_layout(c, &s64));
   LSQ2L_HIP_TRY(hipStreamSynchronize(st));
+  work.release();
   c->info.t_assemble_ms = ms_since(t0);
   // --- batched local Cholesky: the selection's factors (FP64, [I, Gamma])
   // on st; then the solve factors (FP64, or FP32 on MFMA in the mixed path)
@@ -955,8 +963,11 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
     launch_chol_local(st, nparts, c->P, H.total_fac / TT, H.total_dinv / TT, c->fac, c->dinv, c->status,
                       c->solve_plan);
     if (!c->solve_plan) {
-      TRY(solve_stream(c, st));
-      pack_solve_stream(c, st);
+      TRY(solve_cols(c, st));
+      if (!c->lean) {
+        TRY(solve_stream(c, st));
+        pack_solve_stream(c, st);
+      }
     }
   }
   if (c->solve_plan) {
@@ -997,8 +1008,11 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
       launch_chol_local(c->st2, nparts, c->Ps, c->s_total_fac / TT, c->s_total_tiles, c->sfac, c->sdinv,
                         c->status + 2);
     }
-    TRY(solve_stream(c, c->st2));
-    pack_solve_stream(c, c->st2);
+    TRY(solve_cols(c, c->st2));
+    if (!c->lean) {
+      TRY(solve_stream(c, c->st2));
+      pack_solve_stream(c, c->st2);
+    }
     LSQ2L_HIP_TRY(hipEventRecord(c->ev_join, c->st2));
   }
   if (qr)
@@ -1038,7 +1052,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
       launch_chol_local(st, nparts, c->Ps, c->s_total_fac / TT, c->s_total_tiles, s64, d64, c->status + 3);
       launch_to_float(st, c->s_total_fac, s64, c->fac32);
       launch_to_float(st, c->s_total_dinv, d64, c->dinv32);
-      pack_solve_stream(c, st);
+      if (c->ss.cap > 0) pack_solve_stream(c, st);
       LSQ2L_HIP_TRY(hipMemcpyAsync(&hs, c->status + 3, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       LSQ2L_HIP_TRY(hipStreamSynchronize(st));
       if (hs != 0) {
@@ -1288,7 +1302,7 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
     Mi.nnz = nnz;
     Mi.spmv_group = c->M.spmv_group;
     Mi.spmvt_group = c->M.spmvt_group;
-    TRY(c->dalloc(&c->mi_y, m));
+    if (!c->lean) TRY(c->dalloc(&c->mi_y, m));
     TRY(c->dalloc(&Mi.colind, nnz));
     TRY(c->dalloc(&Mi.vals, nnz));
     TRY(c->dalloc(&Mi.trowptr, (int64_t)n + 1));
@@ -1298,12 +1312,12 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
     if (D.done) {
       TRY(c->dalloc(&Mi.rowptr, (int64_t)m + 1));
       TRY(c->dalloc(&c->mi_perm, m));
-      TRY(row_order_device(c, work, c->mi_perm, Mi.rowptr));
+      TRY(row_order_device(c, sort, c->mi_perm, Mi.rowptr));
     } else {
       TRY(c->upload(&c->mi_perm, ro.perm));
       TRY(c->upload(&Mi.rowptr, ro.prp));
     }
-    TRY(transpose_space(sort, nnz, n, &temp, &tb));
+    TRY(transpose_space(sort, c->lean, nnz, n, &temp, &tb));
     launch_permute_rows(st, m, c->mi_perm, c->M.rowptr, c->M.colind, c->M.vals, Mi.rowptr, Mi.colind, Mi.vals);
     LSQ2L_HIP_TRY(launch_transpose(st, m, n, nnz, Mi.rowptr, Mi.colind, Mi.vals, Mi.trowptr, Mi.trow,
                                    Mi.tvals, Mi.tperm, temp, tb));
@@ -1359,7 +1373,26 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   TRY(finish_solve_factors());
   LSQ2L_HIP_TRY(hipStreamSynchronize(st));
   // The streams hold what the local solves read, and the coarse space is there:
-  // the factors are read no more, unless a subdomain lies beyond the streams
+  // the factors are read no more, unless a subdomain lies beyond the streams (or
+  // there are none: a lean setup makes them now if they fit, in place of the
+  // factors that only the selection reads)
+  if (c->lean) {
+    if (c->solve_plan) {
+      c->give_back(c->fac);
+      c->give_back(c->dinv);
+    }
+    sort.release();
+    cache_release();
+    const lsq2l_ctx::Mark before = c->mark();
+    if (solve_stream(c, st) == LSQ2L_OK) {
+      pack_solve_stream(c, st);
+    } else {
+      g_err.clear();
+      c->rollback(before);
+      c->ss.cap = 0;
+    }
+    LSQ2L_HIP_TRY(hipStreamSynchronize(st));
+  }
   if (*std::max_element(c->solve_np.begin(), c->solve_np.end()) <= c->ss.cap) {
     c->give_back(c->fac);
     c->give_back(c->dinv);
@@ -1506,7 +1539,7 @@ lsq2l_status setup_instances(lsq2l_ctx* c, int count, const lsq2l_problem* probs
   // pointers and parts are waited for here)
   HostPattern pat;
   hipError_t e = hipSuccess;
-  if (NNZ < DEVICE_PLAN_NNZ) TRY(pat.start(c));
+  if (c->lean || NNZ < DEVICE_PLAN_NNZ) TRY(pat.start(c));
   else e = hipStreamSynchronize(st);
   if (e != hipSuccess) { set_error(std::string("reading A: ") + hipGetErrorString(e)); return LSQ2L_EHIP; }
   // the first failure in the order of the checks: row extents, then columns
@@ -1566,6 +1599,26 @@ lsq2l_ctx* new_handle(double tau, const lsq2l_options* opt, void* hip_stream) {
   if (opt) c->opt = *opt;
   c->tau = tau;
   return c;
+}
+
+// Setup of a handle.  One that device memory does not suffice for is set up
+// again from the start in the least memory (lsq2l_ctx::lean): the device planner's
+// lists, the table of owners and the wide sorts take up to 70 bytes per entry of A
+// for a time, the streams twice the solve factors beside them.
+lsq2l_status setup_handle(int count, const lsq2l_problem* probs, double tau, const lsq2l_options* opt,
+                          void* hip_stream, lsq2l_handle* out) {
+  lsq2l_status s = LSQ2L_OK;
+  for (bool lean : {false, true}) {
+    lsq2l_ctx* c = new_handle(tau, opt, hip_stream);
+    c->lean = lean;
+    s = setup_instances(c, count, probs);
+    if (s == LSQ2L_OK) { *out = c; return s; }
+    delete c;
+    if (s != LSQ2L_ENOMEM) return s;
+    cache_release();
+    if (!lean) g_err.clear();
+  }
+  return s;
 }
 
 lsq2l_status autotune_spmv(lsq2l_ctx* c, int reps) {
@@ -1663,11 +1716,7 @@ lsq2l_status lsq2l_setup(int64_t m, int64_t n, int64_t nnz, const int64_t* rowpt
   lsq2l_problem pr{};
   pr.m = m; pr.n = n; pr.nnz = nnz;
   pr.rowptr = rowptr; pr.colind = colind; pr.vals = vals; pr.part = part; pr.nparts = nparts;
-  lsq2l_ctx* c = new_handle(tau, opt, hip_stream);
-  const lsq2l_status s = setup_instances(c, 1, &pr);
-  if (s != LSQ2L_OK) { delete c; return s; }
-  *out = c;
-  return LSQ2L_OK;
+  return setup_handle(1, &pr, tau, opt, hip_stream, out);
 }
 
 lsq2l_status lsq2l_setup_batched(int32_t count, const lsq2l_problem* probs, double tau,
@@ -1676,11 +1725,7 @@ lsq2l_status lsq2l_setup_batched(int32_t count, const lsq2l_problem* probs, doub
   if (!out || !probs || count < 1) { set_error("bad arguments"); return LSQ2L_EINVAL; }
   *out = nullptr;
   TRY(check_common(tau, opt));
-  lsq2l_ctx* c = new_handle(tau, opt, hip_stream);
-  const lsq2l_status s = setup_instances(c, count, probs);
-  if (s != LSQ2L_OK) { delete c; return s; }
-  *out = c;
-  return LSQ2L_OK;
+  return setup_handle(count, probs, tau, opt, hip_stream, out);
 }
 
 lsq2l_status lsq2l_solve(lsq2l_handle c, const double* b, double* x, lsq2l_solve_info* info) {
@@ -1806,8 +1851,9 @@ lsq2l_status lsq2l_time_kernel(lsq2l_handle c, int32_t kernel, int32_t reps, dou
     // result per local unknown
     case 2: {
       std::vector<int32_t> far((size_t)c->nsub * SOLVE_FAR_INTS);
-      LSQ2L_HIP_TRY(hipMemcpyAsync(far.data(), c->ss.far0, far.size() * sizeof(int32_t),
-                                   hipMemcpyDeviceToHost, c->st));
+      if (c->ss.cap > 0)
+        LSQ2L_HIP_TRY(hipMemcpyAsync(far.data(), c->ss.far0, far.size() * sizeof(int32_t),
+                                     hipMemcpyDeviceToHost, c->st));
       LSQ2L_HIP_TRY(hipStreamSynchronize(c->st));
       *bytes = 0.0;
       for (int i = 0; i < c->nsub; ++i) {

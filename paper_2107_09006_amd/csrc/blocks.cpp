@@ -156,7 +156,7 @@ void host_block_give(void* p, size_t bytes) {
 
 using namespace lsq2l;
 
-lsq2l_status lsq2l::device_block(void** v, size_t bytes, size_t* got, int* dev) {
+lsq2l_status lsq2l::device_block(void** v, size_t bytes, size_t* got, int* dev, bool exact) {
   *v = nullptr;
   LSQ2L_HIP_TRY(hipGetDevice(dev));
   // eight sizes per power of two: problems that are alike ask for the same
@@ -165,7 +165,7 @@ lsq2l_status lsq2l::device_block(void** v, size_t bytes, size_t* got, int* dev) 
   // of 96 on new inputs)
   size_t step = (size_t)1 << 20;
   while (step * 16 <= bytes) step *= 2;
-  bytes = (bytes + step - 1) / step * step;
+  if (!exact) bytes = (bytes + step - 1) / step * step;
   if ((*v = cache_take(bytes, *dev, got)) != nullptr) return LSQ2L_OK;
   // a failure is cleared, or the next launch's check would report it
   hipError_t e = hipMalloc(v, bytes);
@@ -186,7 +186,7 @@ lsq2l_status lsq2l::device_block(void** v, size_t bytes, size_t* got, int* dev) 
 
 lsq2l_status lsq2l_ctx::raw_alloc(void** v, size_t bytes) {
   DevBlock b{};
-  TRY(device_block(&b.p, bytes, &b.bytes, &b.dev));
+  TRY(device_block(&b.p, bytes, &b.bytes, &b.dev, lean));
   dev_allocs.push_back(b);
   *v = b.p;
   return LSQ2L_OK;

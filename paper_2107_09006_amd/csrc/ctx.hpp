@@ -26,8 +26,9 @@ inline double ms_since(clk::time_point t0) {
 // Device blocks of destroyed handles, kept for later handles on the same
 // device (blocks.cpp).
 void* cache_take(size_t bytes, int dev, size_t* got);
-// a block of at least the given size on the current device, from the cache or new
-lsq2l_status device_block(void** p, size_t bytes, size_t* got, int* dev);
+// a block of at least the given size on the current device, from the cache or
+// new; exact: no larger than asked if it is new
+lsq2l_status device_block(void** p, size_t bytes, size_t* got, int* dev, bool exact = false);
 void cache_give(void* p, size_t bytes, int dev);
 void cache_release();
 
@@ -155,6 +156,11 @@ struct lsq2l_ctx {
   lsq2l_setup_info info{};
   struct DevBlock { void* p; size_t bytes; int dev; bool chunk = false; };   // chunk: of the arena
   std::vector<DevBlock> dev_allocs;
+  // Setup in the least memory (see setup_handle): blocks as large as asked, the
+  // host planner, no table of the entries' owners, the least work space of the
+  // sorts, no gathered m-vector, streams of the local solves only if the
+  // finished handle leaves room for them
+  bool lean = false;
   std::vector<void*> host_allocs;
 
   // Device memory of the handle: requests up to ARENA_SMALL bytes are carved

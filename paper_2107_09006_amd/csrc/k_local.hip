@@ -32,7 +32,8 @@ __global__ void k_entry_owner(int64_t nnz, const int32_t* __restrict__ colind, c
 // finished column is written once, zeros included, so the factor array needs
 // no clearing.  Columns with more than NTL stored tiles take several passes over
 // their rows.  owner[e] = (part, local position there) of the column of entry e,
-// gathered once for all subdomains.
+// gathered once for all subdomains; without room for it (OWN false) the column's are
+// looked up.
 // With inv given, it also finds the envelope of C_ii in the global column order
 // (see k_solve_inv): the wave of column a sees every column coupled to it, so
 // the first coupled position of row inv[a] in that order is the minimum it
@@ -49,10 +50,11 @@ __global__ void k_entry_owner(int64_t nnz, const int32_t* __restrict__ colind, c
 // in 1.0) and 4.4 (batch of 3e6 columns, 3 GB); this takes 5.2 and 2.6.
 constexpr int ASM_G = 1024;       // interface columns held in LDS
 constexpr int ASM_MAP = 4096;     // tile rows with a direct slot table
-template <int NTL, int CPW, int LPR>
+template <int NTL, int CPW, int LPR, bool OWN>
 __global__ void __launch_bounds__(256)
 k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
-           const int2* __restrict__ owner,
+           const int2* __restrict__ owner, const int32_t* __restrict__ part,
+           const int32_t* __restrict__ locown,
            const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colind,
            const double* __restrict__ vals, const int32_t* __restrict__ trowptr,
            const int32_t* __restrict__ trow, const double* __restrict__ tvals,
@@ -169,14 +171,15 @@ k_assemble(const SubDesc* __restrict__ subs, const int32_t* __restrict__ omega,
             bool inxi = true;
             if (pass == 1) {
               inxi = false;
-              for (int e = e0 + lane % LPR; e < e1; e += LPR) inxi |= owner[e].x == i;
+              for (int e = e0 + lane % LPR; e < e1; e += LPR) inxi |= (OWN ? owner[e].x : part[colind[e]]) == i;
               const unsigned long long m = __ballot(inxi);
               inxi = (m >> (lane & ~(LPR - 1))) & ((1ull << LPR) - 1ull);
             }
             if (!inxi) continue;
             for (int e = e0 + lane % LPR; e < e1; e += LPR) {
               const double v = vals[e];
-              const int pc = position(colind[e], owner[e]);
+              const int ce = colind[e];
+              const int pc = position(ce, OWN ? owner[e] : int2{part[ce], locown[ce]});
               if (pc < 0) continue;
               if (iv) fmin = min(fmin, iv[pc]);
               if (!A || pc < pos) continue;
@@ -700,8 +703,10 @@ void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix
   // workgroups per subdomain: two tile columns each in a subdomain of 1,024
   // positions, at most 32
   const int ny = std::max(1, std::min(32, P.max_np / (2 * TS)));
-  auto* kernel = M.nnz <= 4 * (int64_t)M.m ? k_assemble<8, 2, 4> : k_assemble<16, 1, 8>;
-  kernel<<<dim3(nsub, ny), 256, 0, st>>>(P.heavy(), P.omega, owner, M.rowptr, M.colind, M.vals, M.trowptr,
+  const bool few = M.nnz <= 4 * (int64_t)M.m;
+  auto* kernel = owner ? (few ? k_assemble<8, 2, 4, true> : k_assemble<16, 1, 8, true>)
+                       : (few ? k_assemble<8, 2, 4, false> : k_assemble<16, 1, 8, false>);
+  kernel<<<dim3(nsub, ny), 256, 0, st>>>(P.heavy(), P.omega, owner, P.part, P.locown, M.rowptr, M.colind, M.vals, M.trowptr,
                                          M.trow, M.tvals, P.tileF, P.tileOff, fac, ctg, inv, gsub, F8, scale);
 }
 

@@ -571,7 +571,8 @@ static size_t stream_lds_bytes(int np, size_t elem) {
 static_assert(SCAP * 8 + 2 * HELPERS * TS * 8 + 2 * SCAP_TILES * 2 <= 160 * 1024, "LDS of the local solve");
 
 // Subdomains above S.cap local unknowns: forward and backward substitution
-// by tile rows with y in global memory, workgroup per subdomain, 32 rows of
+// by tile rows with y in global memory (in LDS up to ycap unknowns, where a handle
+// has no streams), workgroup per subdomain, 32 rows of
 // threads each summing every eighth tile of a row (fixed order), the
 // diagonal blocks applied through their inverses.
 template <typename T>
@@ -580,7 +581,8 @@ k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
               const int64_t* __restrict__ tileOff, const T* __restrict__ fac,
               const T* __restrict__ dinv, SolveStream S, const double* __restrict__ rhs,
               double* __restrict__ loc, const int32_t* __restrict__ sperm,
-              double* __restrict__ scratch) {
+              double* __restrict__ scratch, int ycap) {
+  extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double part[8][TS];
   __shared__ double sv[TS];
   const SubDesc d = subs[blockIdx.x];
@@ -592,7 +594,8 @@ k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
   const int32_t* sp = sperm ? sperm + d.loc_off : nullptr;
   // y in global memory: in place in loc, or, for a permuted layout, in the
   // subdomain's slice of scratch
-  double* y = sp ? scratch + d.loc_off : loc + d.loc_off;
+  const bool lds = d.np <= ycap;
+  double* y = lds ? reinterpret_cast<double*>(smem) : sp ? scratch + d.loc_off : loc + d.loc_off;
   const int tid = threadIdx.x;
   const int32_t* col = S.scol + d.loc_off;
   const double* sc = S.sscale + d.loc_off;
@@ -644,7 +647,7 @@ k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
     __syncthreads();
   }
   for (int q = tid; q < d.np; q += blockDim.x)
-    if (!sp) y[q] *= sc[q];
+    if (!sp) loc[d.loc_off + q] = sc[q] * y[q];
     else if (sp[q] >= 0) loc[sp[q]] = sc[q] * y[q];
 }
 
@@ -680,11 +683,13 @@ template <typename T>
 void launch_local_solve(hipStream_t st, int nsub, const DevPlan& P, const SolveStream& S, const T* fac,
                         const T* dinv, const double* r, double* loc) {
   const size_t lds = stream_lds_bytes(std::min(P.max_np, S.cap), sizeof(T));
-  k_local_solve_stream<T><<<nsub, 64 * SOLVE_WAVES, lds, st>>>(P.heavy(), S, (const T*)S.fwd, (const T*)S.bwd,
+  if (S.cap > 0)
+    k_local_solve_stream<T><<<nsub, 64 * SOLVE_WAVES, lds, st>>>(P.heavy(), S, (const T*)S.fwd, (const T*)S.bwd,
                                                   (const T*)S.dpack, r, loc, P.sperm);
+  const int ycap = S.cap > 0 ? 0 : std::min(P.max_np, SCAP);
   if (P.max_np > S.cap)
-    k_local_solve<T><<<nsub, 256, 0, st>>>(P.subs, P.tileF, P.tileOff, fac, dinv, S, r, loc, P.sperm,
-                                           P.yscratch);
+    k_local_solve<T><<<nsub, 256, (size_t)ycap * sizeof(double), st>>>(
+        P.subs, P.tileF, P.tileOff, fac, dinv, S, r, loc, P.sperm, P.yscratch, ycap);
 }
 template void launch_local_solve<double>(hipStream_t, int, const DevPlan&, const SolveStream&,
                                          const double*, const double*, const double*, double*);
@@ -699,6 +704,9 @@ hipError_t local_solve_configure() {
     e = hipFuncSetAttribute((const void*)k_local_solve_stream<float>,
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)stream_lds_bytes(SCAP_OF<float>, sizeof(float)));
+  for (const void* k : {(const void*)k_local_solve<double>, (const void*)k_local_solve<float>})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SCAP * (int)sizeof(double));
   return e;
 }
 

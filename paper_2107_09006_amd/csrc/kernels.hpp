@@ -48,7 +48,7 @@ constexpr int SOLVE_FAR_INTS = 14;    // entries of SolveStream::far0 per subdom
 // What the local solves read (k_solve.hip): the streams of both sweeps and
 // the packed diagonal inverses, in the type of the factors, with their tables
 struct SolveStream {
-  int cap = 0;                            // largest padded subdomain that they solve
+  int cap = 0;                            // largest padded subdomain that they solve (0: none are there)
   void *fwd = nullptr, *bwd = nullptr;    // as many entries as the factor's envelope, and a tile
   void* dpack = nullptr;                  // SOLVE_DPACK entries per diagonal tile
   uint16_t* nfar[2] = {nullptr, nullptr}; // slabs of every step (tile_base + step)
@@ -262,7 +262,7 @@ void launch_perm_len(hipStream_t st, int32_t m, const int32_t* perm, const int32
 // scale non-null: assemble S C_ii S and S Ct_GG S directly (S = scale, from
 // launch_col_scale), identity on the padding diagonal
 // owner: per entry of A the part and local position of its column
-// (launch_entry_owner); fac need not be cleared
+// (launch_entry_owner), or null: looked up; fac need not be cleared
 void launch_entry_owner(hipStream_t st, const DevPlan& P, const DevMatrix& M, int2* owner);
 void launch_assemble(hipStream_t st, int nsub, const DevPlan& P, const DevMatrix& M, const int2* owner,
                      double* fac, double* ctg, const int32_t* inv, const SubDesc* gsub, int32_t* F8,

@@ -21,9 +21,9 @@ struct Scratch {
     blocks.clear();
   }
   template <typename T>
-  lsq2l_status alloc(T** p, int64_t count) {
+  lsq2l_status alloc(T** p, int64_t count, bool exact = false) {
     lsq2l_ctx::DevBlock b{};
-    lsq2l_status s = device_block(&b.p, (size_t)std::max<int64_t>(count, 1) * sizeof(T), &b.bytes, &b.dev);
+    lsq2l_status s = device_block(&b.p, (size_t)std::max<int64_t>(count, 1) * sizeof(T), &b.bytes, &b.dev, exact);
     if (s == LSQ2L_OK) blocks.push_back(b);
     *p = (T*)b.p;
     return s;
@@ -33,11 +33,11 @@ struct Scratch {
 // Work space of a transpose of nnz entries and n columns: what carries rows and
 // values through the sort, or where that cannot be had the least (a third of it;
 // rows and values are gathered then, see launch_transpose)
-inline lsq2l_status transpose_space(Scratch& s, int64_t nnz, int32_t n, char** temp, size_t* bytes) {
+inline lsq2l_status transpose_space(Scratch& s, bool lean, int64_t nnz, int32_t n, char** temp, size_t* bytes) {
   *bytes = transpose_temp_bytes(nnz, n);
-  if (s.alloc(temp, (int64_t)*bytes) == LSQ2L_OK) return LSQ2L_OK;
+  if (!lean && s.alloc(temp, (int64_t)*bytes) == LSQ2L_OK) return LSQ2L_OK;
   *bytes = transpose_temp_least(nnz, n);
-  return s.alloc(temp, (int64_t)*bytes);
+  return s.alloc(temp, (int64_t)*bytes, lean);
 }
 
 // From this many entries on the device plans: some thirty launches and six

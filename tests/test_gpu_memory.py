@@ -99,3 +99,39 @@ def test_handle_keeps_one_copy_of_the_factors(precision):
     assert two > 512 * MiB
     s.close()
     assert held <= (two + 28 * p.nnz) * 9 / 8 + 512 * MiB
+
+
+def _problem(kind):
+    from workloads import generators as W
+    if kind == "wide":            # up to four entries per row
+        return W.random_banded(160000, 320000, 40, seed=9, half_width=200)
+    return W.irregular_clustered(100000, 300000, 50, seed=5)      # more, and a row-permuted copy
+
+
+# MiB free: enough for the least setup, with room for the streams of the local
+# solves in the finished handle (3100, 2000) or without (2600, 1450); a setup with
+# plenty takes 4,780 and 2,580
+@pytest.mark.parametrize("kind,precision,mib", [("wide", "fp64", 3100), ("wide", "fp64", 2600), ("wide", "mixed", 2900),
+                                                ("irregular", "fp64", 2000), ("irregular", "fp64", 1450)])
+def test_setup_with_little_memory(kind, precision, mib):
+    """Products against scipy to rounding (n eps of the sum of magnitudes), and the
+    solve's true residual with its own tolerance."""
+    import torch
+    import paper_2107_09006_amd as L
+    p = _problem(kind)
+    A = p.scipy()
+    dev = [torch.as_tensor(a).cuda() for a in (p.indptr.astype(np.int32), p.indices, p.data)]
+    b = torch.as_tensor(p.b).cuda()
+    v = torch.as_tensor(np.random.default_rng(2).standard_normal(p.n)).cuda()
+    with _left(mib * MiB):
+        s = L.Solver(*dev, p.part, p.nparts, p.m, p.n, p.tau,
+                     precision=L.FP64 if precision == "fp64" else L.MIXED)
+        x, info, _ = s.solve(b)
+        Av, Ab = s.spmv(v), s.spmv(b, True)
+        s.close()
+    eps = np.finfo(float).eps
+    for got, M, u in ((Av, A, v), (Ab, A.T.tocsr(), b)):
+        u = u.cpu().numpy()
+        assert np.all(np.abs(got.cpu().numpy() - M @ u) <= M.shape[1] * eps * (abs(M) @ np.abs(u)))
+    x = x.cpu().numpy()
+    assert np.linalg.norm(A.T @ (p.b - A @ x)) <= 10 * p.tol * np.linalg.norm(A.T @ p.b)
