@@ -1347,9 +1347,26 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   TRY(c->dalloc(&c->partial, 2 * (int64_t)S * RED_BLOCKS));
   TRY(c->dalloc(&c->sums, S));
   {
-    const int64_t len = (int64_t)std::min(S, RED_TOTAL / 2) * COUNT_LEN;
-    TRY(c->dalloc(&c->red_count, len));
-    launch_fill_i32(st, len, 0, c->red_count);
+    int64_t slots = 1;
+    std::vector<Chunk> all;
+    std::vector<std::pair<Chunks*, int64_t>> at;      // cuts and their first entries
+    auto cut = [&](Chunks& out, const std::vector<int64_t>& seg, int64_t size, int64_t most) {
+      const std::vector<Chunk> v = make_chunks(seg, size, most);
+      if (most == RED_BLOCKS)
+        for (const Chunk& k : v) slots = std::max<int64_t>(slots, k.slot + 1);
+      out.n = (int32_t)v.size();
+      at.push_back({&out, (int64_t)all.size()});
+      all.insert(all.end(), v.begin(), v.end());
+    };
+    cut(c->col_red, c->seg_col_h, reduction_chunk(n), RED_BLOCKS);
+    cut(c->col_fine, c->seg_col_h, 1024, INT64_MAX);
+    if (c->opt.krylov == LSQ2L_LSQR) cut(c->row_red, c->seg_row_h, reduction_chunk(m), RED_BLOCKS);
+    if (c->opt.krylov == LSQ2L_GMRES) cut(c->col_mdot, c->seg_col_h, reduction_chunk(n), MDOT_BLOCKS);
+    Chunk* table = nullptr;
+    TRY(c->upload(&table, all));
+    for (auto& k : at) k.first->c = table + k.second;
+    TRY(c->dalloc(&c->red_count, slots * COUNT_LEN));
+    launch_fill_i32(st, slots * COUNT_LEN, 0, c->red_count);
   }
   double* scal = nullptr;
   TRY(c->dalloc(&scal, 6 * (int64_t)S));
@@ -1363,10 +1380,6 @@ lsq2l_status setup_core(lsq2l_ctx* c, HostPattern& pat, const HostVec<int32_t>& 
   TRY(c->halloc(&c->h_r0n2, S));
   TRY(c->halloc(&c->h_part, S));
   c->sc.h_done = c->h_done;
-  for (int s = 0; s < S; ++s) {
-    c->max_seg_col = std::max(c->max_seg_col, c->seg_col_h[s + 1] - c->seg_col_h[s]);
-    c->max_seg_row = std::max(c->max_seg_row, c->seg_row_h[s + 1] - c->seg_row_h[s]);
-  }
   TRY(c->upload(&c->d_seg_col, c->seg_col_h));
   TRY(c->upload(&c->d_seg_row, c->seg_row_h));
   TRY(krylov_alloc(c));

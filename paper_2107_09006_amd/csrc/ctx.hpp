@@ -96,9 +96,9 @@ struct lsq2l_ctx {
   std::vector<int64_t> seg_row_h, seg_col_h;
   int64_t* d_seg_row = nullptr;
   int64_t* d_seg_col = nullptr;
-  int64_t max_seg_row = 0, max_seg_col = 0;   // the longest instance
-  lsq2l::Segments rows() const { return {d_seg_row, S, max_seg_row}; }
-  lsq2l::Segments cols() const { return {d_seg_col, S, max_seg_col}; }
+  lsq2l::Chunks row_red, col_red, col_fine, col_mdot;   // their cuts (row_red: LSQR, col_mdot: GMRES)
+  lsq2l::Segments rows() const { return {d_seg_row, S, row_red, {}, {}}; }
+  lsq2l::Segments cols() const { return {d_seg_col, S, col_red, col_fine, col_mdot}; }
   lsq2l::DevMatrix M;
   lsq2l::DevMatrix Mi;      // row-permuted copy of A and its transpose for C p = A^T (A p)
   bool row_perm = false;    // Mi is in use

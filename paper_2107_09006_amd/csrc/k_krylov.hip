@@ -2,10 +2,11 @@
 // (eq. normal): C p is applied as A^T (A p), never formed.
 //
 // Reductions are deterministic: every segment (instance) of a vector is cut
-// into chunks whose number depends on the sizes alone, each reduced by a
+// into chunks by its length and that of the whole vector alone, each reduced by a
 // fixed tree; the workgroup that finishes a segment last adds the chunks' sums
 // by another fixed tree and takes the step that needs the sum.  Repeated runs
 // give bitwise-identical results.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -338,9 +339,9 @@ __device__ inline bool count_in(int32_t* cnt, int nblk) {
 // each): with one counter per segment, side by side, a dot product over 64
 // segments of the batch (12,000 workgroups) took 123 us, over one segment of
 // 250,000 7.8 us.
-__device__ inline bool last_block(int32_t* cnt, int nblk, int* sh) {
+__device__ inline bool last_block(int32_t* cnt, int blk, int nblk, int* sh) {
   if (threadIdx.x == 0) {
-    const int g = blockIdx.x / COUNT_GROUP, ng = (nblk + COUNT_GROUP - 1) / COUNT_GROUP;
+    const int g = blk / COUNT_GROUP, ng = (nblk + COUNT_GROUP - 1) / COUNT_GROUP;
     bool last = count_in(cnt + (1 + g) * COUNT_STRIDE, min(COUNT_GROUP, nblk - g * COUNT_GROUP));
     if (last && ng > 1) last = count_in(cnt, ng);
     *sh = last;
@@ -357,16 +358,16 @@ __device__ inline bool last_block(int32_t* cnt, int nblk, int* sh) {
 // columns: 4.7 + 5.6 us -> 6.6; with the update of x and r 4.9 + 4.7 + 5.6 ->
 // 7.8; 64 segments of 3e6 columns in all: 11.5 + 10.2 -> 15.5 and 33 + 11.5 +
 // 10.2 -> 30.
-__device__ inline void finish_reduction(const Reduction& R, int s, double v, double v2, double* sh) {
+__device__ inline void finish_reduction(const Reduction& R, const Chunk& c, double v, double v2, double* sh) {
   __shared__ int flag;
-  const int nb = gridDim.x, t = threadIdx.x;
+  const int s = c.seg, nb = c.n, t = threadIdx.x;
   if (nb > 1) {
     double* P = R.partial + (int64_t)s * 2 * RED_BLOCKS;
     if (t == 0) {
-      agent_store(P + blockIdx.x, v);
-      if (R.two) agent_store(P + RED_BLOCKS + blockIdx.x, v2);
+      agent_store(P + c.k, v);
+      if (R.two) agent_store(P + RED_BLOCKS + c.k, v2);
     }
-    if (!last_block(R.count + (int64_t)s * COUNT_LEN, nb, &flag)) return;
+    if (!last_block(R.count + (int64_t)c.slot * COUNT_LEN, c.k, nb, &flag)) return;
     v = block_reduce_256(t < nb ? agent_load(P + t) : 0.0, sh);
     if (R.two) v2 = block_reduce_256(t < nb ? agent_load(P + RED_BLOCKS + t) : 0.0, sh);
   }
@@ -383,16 +384,14 @@ __device__ inline void finish_reduction(const Reduction& R, int s, double v, dou
 //   RED_AXPY:  o += f a, o2 -= f b, v = o2 o2    (x, r of a CG step; c, if
 //              given, keeps the old o2)
 //   RED_LSQR:  o = a - alpha o on active instances (first: o = a), v = o o
-// Workgroup (b, s) takes chunk b of segment s; every thread has four elements
-// in flight.
+// A workgroup takes a chunk; every thread has four elements in flight.
 template <int KIND>
 __global__ void __launch_bounds__(256)
-k_reduce(const int64_t* __restrict__ seg_ptr, RedVec V, Reduction R) {
+k_reduce(const Chunk* __restrict__ chunks, RedVec V, Reduction R) {
   __shared__ double sh[4];
-  const int s = blockIdx.y;
-  const int64_t lo = seg_ptr[s], hi = seg_ptr[s + 1];
-  const int64_t chunk = (hi - lo + gridDim.x - 1) / gridDim.x;
-  const int64_t c0 = lo + blockIdx.x * chunk, c1 = min(hi, c0 + chunk);
+  const Chunk c = chunks[blockIdx.x];
+  const int s = c.seg;
+  const int64_t c0 = c.lo, c1 = c.lo + c.len;
   const double* __restrict__ a = V.a;
   const double* __restrict__ b = V.b;
   double* __restrict__ o = V.o;
@@ -457,27 +456,44 @@ k_reduce(const int64_t* __restrict__ seg_ptr, RedVec V, Reduction R) {
   for (; k < c1; k += 256) elements(k, std::integral_constant<int, 1>{});
   v = block_reduce_256(v, sh);
   if constexpr (KIND == RED_DOT2) v2 = block_reduce_256(v2, sh);
-  finish_reduction(R, s, v, v2, sh);
+  finish_reduction(R, c, v, v2, sh);
 }
 
-// Chunks per segment: 1,024 elements each (four per thread), at most
-// RED_BLOCKS, and at most RED_TOTAL workgroups over all segments.  A segment
-// of up to 1,024 elements is one workgroup, with no exchange between any.
-static unsigned red_chunks(const Segments& G, int64_t most) {
-  const int64_t total = std::max<int64_t>(1, RED_TOTAL / G.S);
-  return (unsigned)std::max<int64_t>(1, std::min<int64_t>({most, total, (G.maxlen + 1023) / 1024}));
+// A segment's chunks: size elements each, at most most of them (then larger ones),
+// at least one.  Reductions: 1,024 elements (four per thread), or as many as keep
+// the whole vector to RED_TOTAL chunks, and at most RED_BLOCKS per segment, so
+// that a long segment gets its workgroups whatever lies beside it: 4,200 segments of
+// 32 elements beside one of 1e6 took one workgroup for it when RED_TOTAL was split
+// evenly.  A segment of one chunk has no exchange between workgroups.
+std::vector<Chunk> make_chunks(const std::vector<int64_t>& seg, int64_t size, int64_t most) {
+  std::vector<Chunk> out;
+  int32_t slots = 0;
+  for (size_t s = 0; s + 1 < seg.size(); ++s) {
+    const int64_t len = seg[s + 1] - seg[s];
+    const int64_t n = std::max<int64_t>(1, std::min(most, (len + size - 1) / size));
+    const int64_t per = (len + n - 1) / n;
+    const int32_t slot = n > 1 ? slots++ : 0;
+    for (int64_t k = 0; k < n; ++k) {
+      const int64_t lo = std::min(len, k * per);
+      out.push_back(Chunk{seg[s] + lo, (int32_t)(std::min(len, lo + per) - lo), (int32_t)s, (int32_t)k, (int32_t)n, slot, 0});
+    }
+  }
+  return out;
 }
+
+int64_t reduction_chunk(int64_t total) { return std::max<int64_t>(1024, (total + RED_TOTAL - 1) / RED_TOTAL); }
 
 void launch_reduce(hipStream_t st, int kind, const Segments& G, const RedVec& V, const Reduction& R) {
-  const dim3 grid(red_chunks(G, RED_BLOCKS), G.S);
+  const unsigned grid = (unsigned)G.red.n;
+  const Chunk* c = G.red.c;
   switch (kind) {
-    case RED_DOT: k_reduce<RED_DOT><<<grid, 256, 0, st>>>(G.ptr, V, R); break;
-    case RED_DOT2: k_reduce<RED_DOT2><<<grid, 256, 0, st>>>(G.ptr, V, R); break;
-    case RED_COPY: k_reduce<RED_COPY><<<grid, 256, 0, st>>>(G.ptr, V, R); break;
-    case RED_START: k_reduce<RED_START><<<grid, 256, 0, st>>>(G.ptr, V, R); break;
-    case RED_SUB: k_reduce<RED_SUB><<<grid, 256, 0, st>>>(G.ptr, V, R); break;
-    case RED_AXPY: k_reduce<RED_AXPY><<<grid, 256, 0, st>>>(G.ptr, V, R); break;
-    default: k_reduce<RED_LSQR><<<grid, 256, 0, st>>>(G.ptr, V, R);
+    case RED_DOT: k_reduce<RED_DOT><<<grid, 256, 0, st>>>(c, V, R); break;
+    case RED_DOT2: k_reduce<RED_DOT2><<<grid, 256, 0, st>>>(c, V, R); break;
+    case RED_COPY: k_reduce<RED_COPY><<<grid, 256, 0, st>>>(c, V, R); break;
+    case RED_START: k_reduce<RED_START><<<grid, 256, 0, st>>>(c, V, R); break;
+    case RED_SUB: k_reduce<RED_SUB><<<grid, 256, 0, st>>>(c, V, R); break;
+    case RED_AXPY: k_reduce<RED_AXPY><<<grid, 256, 0, st>>>(c, V, R); break;
+    default: k_reduce<RED_LSQR><<<grid, 256, 0, st>>>(c, V, R);
   }
 }
 
@@ -490,13 +506,13 @@ __device__ inline int seg_of(int64_t k, int S, const int64_t* seg_ptr) {
   return lo;
 }
 
-// p = z + beta p, workgroup (b, s) on 1,024 elements of segment s
+// p = z + beta p, a workgroup per piece of up to 1,024 elements
 __global__ void __launch_bounds__(256)
-k_xpby(const int64_t* __restrict__ seg_ptr, const double* __restrict__ beta,
+k_xpby(const Chunk* __restrict__ fine, const double* __restrict__ beta,
        const double* __restrict__ z, double* __restrict__ p) {
-  const int s = blockIdx.y;
-  const int64_t k0 = seg_ptr[s] + (int64_t)blockIdx.x * 1024 + threadIdx.x, hi = seg_ptr[s + 1];
-  const double b = beta[s];
+  const Chunk c = fine[blockIdx.x];
+  const int64_t k0 = c.lo + threadIdx.x, hi = c.lo + c.len;
+  const double b = beta[c.seg];
   double zv[4], pv[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u)
@@ -510,8 +526,7 @@ k_xpby(const int64_t* __restrict__ seg_ptr, const double* __restrict__ beta,
 }
 
 void launch_xpby(hipStream_t st, const Segments& G, const double* beta, const double* z, double* p) {
-  if (G.maxlen == 0) return;
-  k_xpby<<<dim3((unsigned)((G.maxlen + 1023) / 1024), G.S), 256, 0, st>>>(G.ptr, beta, z, p);
+  k_xpby<<<(unsigned)G.fine.n, 256, 0, st>>>(G.fine.c, beta, z, p);
 }
 
 __global__ void k_sub(int64_t n, const double* __restrict__ a, const double* __restrict__ b,
@@ -672,18 +687,17 @@ void launch_lsqr_update(hipStream_t st, int64_t n, int S, const int64_t* seg_col
 // the other with a barrier each, and one thread per vector adding 256 partial
 // sums, took 13.4 + 16.5 us per pass (mean over 1 to 30 vectors of 90,601); this
 // takes 7.5.
-constexpr int MDOT_BLOCKS = 64;   // chunks: the groups of eight vectors fill the chip too
+// Its segments have at most 64 chunks: the groups of eight vectors fill the chip too.
 __global__ void __launch_bounds__(256)
-k_multidot(const int64_t* __restrict__ seg_ptr, int64_t n, int kv, const double* __restrict__ V,
+k_multidot(const Chunk* __restrict__ chunks, int64_t n, int kv, const double* __restrict__ V,
            const double* __restrict__ w, double* __restrict__ partial, int32_t* __restrict__ count,
            int ld, double* __restrict__ h, double* __restrict__ sum) {
   __shared__ double sh[4][MDOT];
   __shared__ int flag;
-  const int s = blockIdx.y, i0 = blockIdx.z * MDOT, nv = min(MDOT, kv - i0), nb = gridDim.x;
+  const Chunk ch = chunks[blockIdx.x];
+  const int s = ch.seg, i0 = blockIdx.y * MDOT, nv = min(MDOT, kv - i0), nb = ch.n;
   const int t = threadIdx.x, lane = t % 64, wave = t / 64;
-  const int64_t lo = seg_ptr[s], hi = seg_ptr[s + 1];
-  const int64_t chunk = (hi - lo + nb - 1) / nb;
-  const int64_t c0 = lo + blockIdx.x * chunk, c1 = min(hi, c0 + chunk);
+  const int64_t c0 = ch.lo, c1 = ch.lo + ch.len;
   const double* v[MDOT];
   double acc[MDOT];
 #pragma unroll
@@ -705,11 +719,11 @@ k_multidot(const int64_t* __restrict__ seg_ptr, int64_t n, int kv, const double*
   double* P = partial + ((int64_t)s * ld + i0) * MDOT_BLOCKS;
   if (wave == 0) {
     if (lane < nv)
-      agent_store(P + (int64_t)lane * MDOT_BLOCKS + blockIdx.x,
+      agent_store(P + (int64_t)lane * MDOT_BLOCKS + ch.k,
                   (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]));
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // all lanes' stores, before the count
   }
-  if (t == 0) flag = count_in(count + ((int64_t)s * gridDim.z + blockIdx.z) * COUNT_STRIDE, nb);
+  if (t == 0) flag = count_in(count + ((int64_t)s * gridDim.y + blockIdx.y) * COUNT_STRIDE, nb);
   __syncthreads();
   if (!flag) return;
   for (int i = wave; i < nv; i += 4) {
@@ -725,8 +739,8 @@ void launch_multidot(hipStream_t st, const Segments& G, int64_t n, int k, const 
                      const double* w, double* partial, int32_t* count, int ld, double* h,
                      double* sum) {
   if (k == 0) return;
-  const dim3 grid(red_chunks(G, MDOT_BLOCKS), G.S, (k + MDOT - 1) / MDOT);
-  k_multidot<<<grid, 256, 0, st>>>(G.ptr, n, k, V, w, partial, count, ld, h, sum);
+  const dim3 grid((unsigned)G.mdot.n, (k + MDOT - 1) / MDOT);
+  k_multidot<<<grid, 256, 0, st>>>(G.mdot.c, n, k, V, w, partial, count, ld, h, sum);
 }
 
 // out_k (-)= sum_i V_i[k] c[seg(k) * ld + i]

@@ -133,16 +133,29 @@ void launch_grad_vals(hipStream_t st, int32_t m, const int32_t* rowptr, const in
 
 // --- vector / reduction kernels --------------------------------------------
 constexpr int RED_BLOCKS = 256;   // most partial sums per segment
-constexpr int RED_TOTAL = 8192;   // most workgroups of a reduction with more than one per segment
+constexpr int RED_TOTAL = 8192;   // workgroups of a reduction beyond which the chunks grow
+constexpr int MDOT_BLOCKS = 64;   // most chunks per segment of the Gram-Schmidt products
 // counters of the workgroups of a segment: one per COUNT_GROUP of them and
 // one for the groups, COUNT_STRIDE int32 apart (128 bytes)
 constexpr int COUNT_GROUP = 16, COUNT_STRIDE = 32;
 constexpr int COUNT_LEN = (1 + RED_BLOCKS / COUNT_GROUP) * COUNT_STRIDE;
-// the instances' parts of a concatenated vector (device offsets), and the longest
+// A workgroup's part of a concatenated vector: len elements from lo, chunk k of
+// the n chunks of instance seg; slot: its counters, where n > 1
+struct Chunk {
+  int64_t lo;
+  int32_t len, seg, k, n, slot, unused;
+};
+struct Chunks {
+  const Chunk* c = nullptr;   // device table
+  int32_t n = 0;
+};
+// The instances' parts of a concatenated vector (device offsets) and their cuts:
+// into chunks of a reduction, into pieces of 1,024 elements, and into chunks of
+// the Gram-Schmidt products.  Every instance has at least one of each.
 struct Segments {
   const int64_t* ptr;
   int S;
-  int64_t maxlen;
+  Chunks red, fine, mdot;
 };
 enum ScalarOp { OP_R0 = 0, OP_RHO_INIT = 1, OP_ALPHA = 2, OP_RNORM = 3, OP_BETA = 4, OP_SUM = 5,
                 LSQR_INIT_BETA = 8, LSQR_INIT_ALPHA = 9, LSQR_BETA = 10, LSQR_ALPHA = 11 };
@@ -158,8 +171,7 @@ enum LsqrSc { LS_ALPHA = 0, LS_BETA, LS_RHOBAR, LS_PHIBAR, LS_ANORM2, LS_T1, LS_
 constexpr int LSQR_NSC = LS_NSC;
 // What a reduction does with its sums (per segment): op, and its operands.
 // partial holds 2 RED_BLOCKS doubles per segment; count COUNT_LEN int32 per
-// segment, zero between launches (with more than RED_TOTAL / 2 segments every
-// segment is one workgroup, and none of the two is touched).
+// slot (segment of more than one chunk), zero between launches.
 struct Reduction {
   int op;
   int two;            // the pass forms two sums
@@ -177,6 +189,9 @@ struct RedVec {
   double *o = nullptr, *o2 = nullptr, *keep = nullptr;
   int first = 0;
 };
+// the chunks of the segments seg (host offsets): size elements, at most most per segment
+std::vector<Chunk> make_chunks(const std::vector<int64_t>& seg, int64_t size, int64_t most);
+int64_t reduction_chunk(int64_t total);   // size of a reduction's over a vector of that length
 void launch_reduce(hipStream_t st, int kind, const Segments& G, const RedVec& V, const Reduction& R);
 void launch_xpby(hipStream_t st, const Segments& G, const double* beta, const double* z, double* p);
 void launch_sub(hipStream_t st, int64_t n, const double* a, const double* b, double* out);
