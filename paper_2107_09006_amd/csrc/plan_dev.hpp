@@ -41,9 +41,18 @@ inline lsq2l_status transpose_space(Scratch& s, bool lean, int64_t nnz, int32_t 
 }
 
 // From this many entries on the device plans: some thirty launches and six
-// reads of counts, 0.6 ms at 9,000 entries (host 0.55), 0.8 at 2.7e5 (2.1),
-// 1.2 at 3.8e6 (6.9), 5.5 at 3.3e7 (16).
-constexpr int64_t DEVICE_PLAN_NNZ = (int64_t)1 << 12;
+// reads of counts.  Whole setups in ms, device / host planner, at three kinds of
+// matrix: banded (125 columns per part), grid (20 x 20 per part), irregular (1,000):
+//   4,000 -  7,000 entries   2.06 / 1.89   1.78 / 1.54    5.25 / 5.01
+//   8,700 - 10,700           2.01 / 2.08   2.03 / 1.90   16.3  / 16.2
+//  12,300 - 15,300           2.10 / 2.28   2.27 / 2.11    5.09 / 4.91
+//  17,800 - 21,100           2.09 / 2.56   2.93 / 3.11    6.79 / 6.63
+//  74,000 - 89,000           2.36 / 3.11   3.69 / 4.57   15.8  / 15.9
+// The line lies where the first kind crosses; the others do at 16,000 and 80,000,
+// with less than 5 % between the planners from 12,000 on.  Planning alone: 0.6
+// (0.51) at 9,000 banded entries, 0.88 (2.3) at 3e5, 1.2 (6.9) at 3.8e6, 5.5 (16)
+// at 3.3e7.
+constexpr int64_t DEVICE_PLAN_NNZ = (int64_t)1 << 13;
 // Longest row or column, and largest product of a shared row's length with its
 // number of parts, that a few lanes walk one after the other: some milliseconds
 // (the host planner's threads take such a row in less).
