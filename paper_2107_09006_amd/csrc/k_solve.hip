@@ -570,18 +570,18 @@ static size_t stream_lds_bytes(int np, size_t elem) {
 }
 static_assert(SCAP * 8 + 2 * HELPERS * TS * 8 + 2 * SCAP_TILES * 2 <= 160 * 1024, "LDS of the local solve");
 
-// Subdomains above S.cap local unknowns: forward and backward substitution
-// by tile rows with y in global memory (in LDS up to ycap unknowns, where a handle
-// has no streams), workgroup per subdomain, 32 rows of
+// Subdomains of above lo and up to hi local unknowns: forward and backward
+// substitution by tile rows with y in global memory (with IN_LDS, for handles
+// without streams, in LDS), workgroup per subdomain, 32 rows of
 // threads each summing every eighth tile of a row (fixed order), the
 // diagonal blocks applied through their inverses.
-template <typename T>
+template <typename T, bool IN_LDS>
 __global__ void __launch_bounds__(256)
 k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF,
               const int64_t* __restrict__ tileOff, const T* __restrict__ fac,
               const T* __restrict__ dinv, SolveStream S, const double* __restrict__ rhs,
               double* __restrict__ loc, const int32_t* __restrict__ sperm,
-              double* __restrict__ scratch, int ycap) {
+              double* __restrict__ scratch, int lo, int hi) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double part[8][TS];
   __shared__ double sv[TS];
@@ -590,12 +590,13 @@ k_local_solve(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
   const int64_t* off = tileOff + d.tile_base;
   const T* A = fac + d.fac_off;
   const T* Di = dinv + d.dinv_off;
-  if (d.np <= S.cap) return;                // done by k_local_solve_stream
+  if (d.np <= lo || d.np > hi) return;
   const int32_t* sp = sperm ? sperm + d.loc_off : nullptr;
   // y in global memory: in place in loc, or, for a permuted layout, in the
   // subdomain's slice of scratch
-  const bool lds = d.np <= ycap;
-  double* y = lds ? reinterpret_cast<double*>(smem) : sp ? scratch + d.loc_off : loc + d.loc_off;
+  double* y;
+  if constexpr (IN_LDS) y = reinterpret_cast<double*>(smem);
+  else y = sp ? scratch + d.loc_off : loc + d.loc_off;
   const int tid = threadIdx.x;
   const int32_t* col = S.scol + d.loc_off;
   const double* sc = S.sscale + d.loc_off;
@@ -686,10 +687,13 @@ void launch_local_solve(hipStream_t st, int nsub, const DevPlan& P, const SolveS
   if (S.cap > 0)
     k_local_solve_stream<T><<<nsub, 64 * SOLVE_WAVES, lds, st>>>(P.heavy(), S, (const T*)S.fwd, (const T*)S.bwd,
                                                   (const T*)S.dpack, r, loc, P.sperm);
-  const int ycap = S.cap > 0 ? 0 : std::min(P.max_np, SCAP);
-  if (P.max_np > S.cap)
-    k_local_solve<T><<<nsub, 256, (size_t)ycap * sizeof(double), st>>>(
-        P.subs, P.tileF, P.tileOff, fac, dinv, S, r, loc, P.sperm, P.yscratch, ycap);
+  else
+    k_local_solve<T, true><<<nsub, 256, (size_t)std::min(P.max_np, SCAP) * sizeof(double), st>>>(
+        P.subs, P.tileF, P.tileOff, fac, dinv, S, r, loc, P.sperm, P.yscratch, 0, SCAP);
+  const int done = S.cap > 0 ? S.cap : SCAP;
+  if (P.max_np > done)
+    k_local_solve<T, false><<<nsub, 256, 0, st>>>(P.subs, P.tileF, P.tileOff, fac, dinv, S, r, loc, P.sperm,
+                                                  P.yscratch, done, INT32_MAX);
 }
 template void launch_local_solve<double>(hipStream_t, int, const DevPlan&, const SolveStream&,
                                          const double*, const double*, const double*, double*);
@@ -704,7 +708,7 @@ hipError_t local_solve_configure() {
     e = hipFuncSetAttribute((const void*)k_local_solve_stream<float>,
                             hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)stream_lds_bytes(SCAP_OF<float>, sizeof(float)));
-  for (const void* k : {(const void*)k_local_solve<double>, (const void*)k_local_solve<float>})
+  for (const void* k : {(const void*)k_local_solve<double, true>, (const void*)k_local_solve<float, true>})
     if (e == hipSuccess)
       e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, SCAP * (int)sizeof(double));
   return e;
