@@ -480,6 +480,29 @@ __device__ inline int envelope_rows(const int32_t* F, int J, int ntiles, int32_t
   return *s_count;
 }
 
+// Sum of v over the 256 threads of a block, and the exclusive prefix of each
+// thread (fixed order: waves reduce by shuffles, then the four wave totals).
+__device__ inline int block_excl_scan_256(int v, int* sh, int* total) {
+  const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) sh[w] = x;
+  __syncthreads();
+  int wbase = 0, tot = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (q < w) wbase += sh[q];
+    tot += sh[q];
+  }
+  __syncthreads();
+  *total = tot;
+  return wbase + x - v;
+}
+
 // -------------------------------------------------------------------------
 // host-side helpers shared by the translation units
 // -------------------------------------------------------------------------

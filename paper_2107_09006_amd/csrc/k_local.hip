@@ -511,24 +511,6 @@ __device__ inline int first_tile(const int32_t* f8, int t) {
   return min(min(f8[4 * t], f8[4 * t + 1]), min(f8[4 * t + 2], f8[4 * t + 3])) / TS;
 }
 
-// sum of v over the workgroup's threads before this one; the total in *total
-__device__ inline int block_excl_sum_256(int v, int* sh, int* total) {
-  const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  __syncthreads();
-  if (lane == 63) sh[w] = x;
-  __syncthreads();
-  int before = 0;
-  for (int q = 0; q < w; ++q) before += sh[q];
-  *total = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-  return before + x - v;
-}
-
 // tiles[i] = tiles of the envelope of subdomain i's global-order layout
 __global__ void __launch_bounds__(256)
 k_layout_count(const SubDesc* __restrict__ gsub, const int32_t* __restrict__ F8, int32_t* __restrict__ tiles) {
@@ -537,7 +519,7 @@ k_layout_count(const SubDesc* __restrict__ gsub, const int32_t* __restrict__ F8,
   const int32_t* f8 = F8 + 4 * g.tile_base;
   int v = 0, total = 0;
   for (int t = threadIdx.x; t < g.ntiles; t += 256) v += t - first_tile(f8, t) + 1;
-  (void)block_excl_sum_256(v, sh, &total);
+  (void)block_excl_scan_256(v, sh, &total);
   if (threadIdx.x == 0) tiles[blockIdx.x] = total;
 }
 
@@ -559,7 +541,7 @@ k_layout_fill(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tile
       f = s.spare ? first_tile(f8, t) : tileF[d.tile_base + t];
       n = t - f + 1;
     }
-    const int before = run + block_excl_sum_256(n, sh, &total);
+    const int before = run + block_excl_scan_256(n, sh, &total);
     if (t < s.ntiles) {
       stileF[s.tile_base + t] = f;
       stileOff[s.tile_base + t] = before;

@@ -73,26 +73,6 @@ __device__ inline double dot16(const double* a, const double* b, double init) {
   return (p0 + p1) + (p2 + p3);
 }
 
-// exclusive scan of v over the 256 threads, total in *tot
-__device__ inline int block_scan_256(int v, int* sh, int* tot) {
-  const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-  int x = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sh[wave] = x;
-  __syncthreads();
-  int before = 0, all = 0;
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) before += sh[w];
-    all += sh[w];
-  }
-  __syncthreads();
-  *tot = all;
-  return before + x - v;
-}
-
 }  // namespace
 
 template <int MODE>
@@ -188,7 +168,7 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
       if (c >= 0) len = trowptr[c + 1] - trowptr[c];
     }
     int tot;
-    const int ex = block_scan_256(len, s_scan, &tot);
+    const int ex = block_excl_scan_256(len, s_scan, &tot);
     if (q <= npos) qpre[q] = ncand + ex;
     ncand += tot;
   }
@@ -220,7 +200,7 @@ k_qr_local(const SubDesc* __restrict__ subs, const SubDesc* __restrict__ psubs,
         if (first == lo && (MODE != QR_GAMMA || interior)) take = r;
       }
       int tot;
-      const int ex = block_scan_256(take >= 0 ? 1 : 0, s_scan, &tot);
+      const int ex = block_excl_scan_256(take >= 0 ? 1 : 0, s_scan, &tot);
       if (take >= 0) sBuf[nbuf + ex] = take;
       if (tid == QR_THREADS - 1) s_q = qt;
       __syncthreads();

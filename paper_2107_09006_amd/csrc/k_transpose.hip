@@ -45,29 +45,6 @@ constexpr int SCAN_THREADS = 256, SCAN_ITEMS = 8, SCAN_TILE = SCAN_THREADS * SCA
 // ---------------------------------------------------------------------------
 // exclusive scan of int32 counts (in place), three phases
 // ---------------------------------------------------------------------------
-// Sum of v over the 256 threads of a block, and the exclusive prefix of each
-// thread (fixed order: waves reduce by shuffles, then the four wave totals).
-__device__ inline int block_excl_scan_256(int v, int* sh, int* total) {
-  const int lane = threadIdx.x % 64, w = threadIdx.x / 64;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) sh[w] = x;
-  __syncthreads();
-  int wbase = 0, tot = 0;
-#pragma unroll
-  for (int q = 0; q < SCAN_THREADS / 64; ++q) {
-    if (q < w) wbase += sh[q];
-    tot += sh[q];
-  }
-  __syncthreads();
-  *total = tot;
-  return wbase + x - v;
-}
-
 __global__ void __launch_bounds__(SCAN_THREADS)
 k_scan_tiles(int64_t n, const int32_t* __restrict__ in, int32_t* __restrict__ tile_sum) {
   __shared__ int sh[4];
