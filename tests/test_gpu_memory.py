@@ -105,14 +105,17 @@ def _problem(kind):
     from workloads import generators as W
     if kind == "wide":            # up to four entries per row
         return W.random_banded(160000, 320000, 40, seed=9, half_width=200)
+    if kind == "qr":
+        return W.random_banded(80000, 160000, 40, seed=9, half_width=200)
     return W.irregular_clustered(100000, 300000, 50, seed=5)      # more, and a row-permuted copy
 
 
 # MiB free: enough for the least setup, with room for the streams of the local
 # solves in the finished handle (3100, 2000) or without (2600, 1450); a setup with
-# plenty takes 4,780 and 2,580
+# plenty takes 4,780 and 2,580 (qr: 1850, without streams; 2,580)
 @pytest.mark.parametrize("kind,precision,mib", [("wide", "fp64", 3100), ("wide", "fp64", 2600), ("wide", "mixed", 2900),
-                                                ("irregular", "fp64", 2000), ("irregular", "fp64", 1450)])
+                                                ("irregular", "fp64", 2000), ("irregular", "fp64", 1450),
+                                                ("qr", "fp64", 1850)])
 def test_setup_with_little_memory(kind, precision, mib):
     """Products against scipy to rounding (n eps of the sum of magnitudes), and the
     solve's true residual with its own tolerance."""
@@ -125,7 +128,7 @@ def test_setup_with_little_memory(kind, precision, mib):
     v = torch.as_tensor(np.random.default_rng(2).standard_normal(p.n)).cuda()
     with _left(mib * MiB):
         s = L.Solver(*dev, p.part, p.nparts, p.m, p.n, p.tau,
-                     precision=L.FP64 if precision == "fp64" else L.MIXED)
+                     local_factor=L.FACTOR_QR if kind == "qr" else L.FACTOR_CHOLESKY, precision=L.FP64 if precision == "fp64" else L.MIXED)
         x, info, _ = s.solve(b)
         Av, Ab = s.spmv(v), s.spmv(b, True)
         s.close()
