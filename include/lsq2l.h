@@ -214,6 +214,8 @@ void lsq2l_default_options(lsq2l_options* opt);
  * partition or options, CHOL_BREAKDOWN if a local or the coarse matrix is not
  * numerically positive definite (e.g. A rank deficient and no shift).
  * opt may be NULL (defaults).  On success *out owns all derived device data.
+ * A setup that device memory does not suffice for runs once more in a form that
+ * takes less of it (and longer); ENOMEM if that does not suffice either.
  */
 lsq2l_status lsq2l_setup(int64_t m, int64_t n, int64_t nnz,
                          const int64_t* rowptr, const int32_t* colind, const double* vals,
@@ -331,8 +333,9 @@ lsq2l_status lsq2l_autotune(lsq2l_handle h, int32_t reps, int32_t* lanes);
  * colind (nnz), vals (nnz, may be NULL).  Out: trowptr (n + 1), trow (nnz,
  * row index of each entry of A^T), tvals (nnz, may be NULL), tperm (nnz, may
  * be NULL: the index in A of each entry of A^T).  Runs a stable radix sort by
- * column on `hip_stream`; its work arrays (up to 28 bytes per entry, and the
- * digit counts) come from the library's cache of device memory and go back to
+ * column on `hip_stream`; its work arrays (up to 28 bytes per entry and the
+ * digit counts, or where that cannot be had 12 bytes and narrower digits)
+ * come from the library's cache of device memory and go back to
  * it inside the call (lsq2l_release_cache frees them).  EINVAL on bad sizes or NULL
  * required pointers.  Column indices must lie in [0, n).
  */

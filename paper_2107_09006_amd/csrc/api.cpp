@@ -1490,8 +1490,8 @@ bool is_device_ptr(const void* p) {
 }
 
 // Setup of one or several instances: their CSR arrays are concatenated and
-// checked on the device in three launches (launch_concat), and the
-// concatenated pattern is read back once into pinned memory for the planner.
+// checked on the device in three launches (launch_concat).  The concatenated
+// pattern is read back into pinned memory only where the host is to plan.
 lsq2l_status setup_instances(lsq2l_ctx* c, int count, const lsq2l_problem* probs) {
   auto t_prep = clk::now();
   const hipStream_t st = c->st;

@@ -28,7 +28,10 @@ __global__ void k_entry_owner(int64_t nnz, const int32_t* __restrict__ colind, c
 // Workgroup (i, y) takes the tile columns y, y + gridDim.y, ... of subdomain i,
 // a wave CPW columns at a time: LPR lanes walk the entries of each row of A that
 // holds the column, and every product is added in LDS at its row's place among
-// the column's stored tiles (one wave's adds, in a fixed order).  The
+// the column's stored tiles.  All adds to an entry come from one wave: its steps follow
+// one another, each over up to 64 / (CPW LPR) rows and LPR entries of each, and
+// within a step the LDS adds lanes on one address in an order that is not
+// documented (ascending lanes in every run observed, so results repeat).  The
 // finished column is written once, zeros included, so the factor array needs
 // no clearing.  Columns with more than NTL stored tiles take several passes over
 // their rows.  owner[e] = (part, local position there) of the column of entry e,

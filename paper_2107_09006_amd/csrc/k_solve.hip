@@ -183,8 +183,11 @@ k_stream_layout(const SubDesc* __restrict__ subs, const int32_t* __restrict__ ti
 // The streams' entries from a factor: wave by wave over the tile rows K of a
 // subdomain, the packed D_K and, per tile (K, J), M(K, J) and P(K, J) as 16 x 16
 // MFMA blocks, formed so that the rows of a stored column lie on consecutive
-// lanes.  Operands read across columns are staged in LDS.  Bound by the
-// factor's tiles read once and the streams written once.
+// lanes.  Operands read across columns are staged in LDS.  On wide envelopes it
+// takes several times what the factor read once and the streams written once
+// would (512 irregular subdomains 3.7 ms in FP64, 7.8 in FP32 beside the
+// selection): tile after tile, a wave waits for two operands, forms two products
+// and stores them 16 rows of a column at a time.  64 banded problems 1.6 ms.
 template <typename T>
 __global__ void __launch_bounds__(256, 2)
 k_stream_pack(const SubDesc* __restrict__ subs, const int32_t* __restrict__ tileF,
