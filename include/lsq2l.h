@@ -363,7 +363,8 @@ lsq2l_status lsq2l_transpose_noalloc(int32_t m, int32_t n, int32_t nnz, const in
 
 /* Release every resource of the handle (NULL is ignored).  Its device
  * memory goes to a process-wide cache (at most 32 GiB) that later handles on
- * the same device draw from. */
+ * the same device draw from, as does at the end of a setup what only the setup
+ * needed (about as much again as the handle keeps). */
 void lsq2l_destroy(lsq2l_handle h);
 
 /* Free the device memory held in that cache, and the pinned host buffers
